@@ -205,8 +205,7 @@ nbsgd_status nbsgd_step(float *X, float *V, const float *G, const uint8_t *mask,
 /* nbsgd_step on rows `ld` floats apart: row i of X and V starts at X + i*ld,
  * V + i*ld, and row (i, j) of G at G + (i*m + j)*ld; only the first P floats
  * of a row are read or written (the rest of each row is never touched).
- * ld >= P (NBSGD_E_SHAPE).  The vector width is the largest of 4, 2, 1
- * dividing both P and ld.  nbsgd_step is this call with ld = P.
+ * ld >= P (NBSGD_E_SHAPE).  nbsgd_step is this call with ld = P.
  * Errors: as nbsgd_step.                                                    */
 nbsgd_status nbsgd_step_strided(float *X, float *V, const float *G, int64_t ld,
                                 const uint8_t *mask, const float *W, int32_t n, int32_t m,

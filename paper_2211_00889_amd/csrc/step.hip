@@ -9,10 +9,12 @@
 // fused step).
 // Every kernel works on column tiles: the mix couples learners, never
 // columns, so a workgroup that holds all n rows of its columns can update X in
-// place.  Rows are streamed as VEC-wide vectors (VEC = 4 when P % 4 == 0, else
-// 2 or 1), so each wave moves 64 * VEC * 4 contiguous bytes per row per load.
+// place.  Lanes stream 16 bytes of a row at a time whatever P, the row stride
+// and with them the rows' alignment are (tiles.h), so each wave moves 1 KiB of a
+// row per load; only the last columns of rows that are no multiple of that go
+// one float a lane.
 //
-// Fused step, one workgroup = 8 waves x 64 lanes, one VEC-vector column per
+// Fused step, one workgroup = 8 waves x 64 lanes, four columns (or one) per
 // lane, all n learners; workgroups take the column tiles from the last to the
 // first (the order never changes a result: columns are independent):
 //   phase 1: the finished gradient rows of the tile (sum_i c_i of them, in
@@ -40,6 +42,7 @@
 
 #include "internal.h"
 #include "plan.h"
+#include "tiles.h"
 
 using namespace nbsgd;
 
@@ -56,19 +59,21 @@ constexpr int kStepSlots = (kMaxN + kStepWaves - 1) / kStepWaves;
 static_assert((kMaxN + kMaxRuns) * kWave * 4 * sizeof(float) <= 64 * 1024,
               "fused step LDS exceeds 64 KiB");
 
+// VEC columns in registers and LDS (type), and as they lie in a row of HBM
+// (mem): only float-aligned, since rows of any length start on any float.  The
+// global loads and stores are the same 16-byte instructions either way (gfx950
+// requires no more than dword alignment of them).
 template <int VEC>
 struct Vec;
 template <>
 struct Vec<4> {
   typedef float type __attribute__((ext_vector_type(4)));
-};
-template <>
-struct Vec<2> {
-  typedef float type __attribute__((ext_vector_type(2)));
+  typedef float mem __attribute__((ext_vector_type(4), aligned(4)));
 };
 template <>
 struct Vec<1> {
   typedef float type;
+  typedef float mem;
 };
 
 // Kernel arguments are only ever read as naturally aligned 32-bit words:
@@ -88,34 +93,34 @@ __device__ __forceinline__ int row_of(const Learners& L, int p, int r) {
   return (int)byte_of(L.rows[p], r);
 }
 
-template <typename T>
-__device__ __forceinline__ T ld_stream(const T* p) {
-  return __builtin_nontemporal_load(p);
+template <int VEC>
+__device__ __forceinline__ typename Vec<VEC>::type ld_stream(const float* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const typename Vec<VEC>::mem*>(p));
 }
-template <typename T>
-__device__ __forceinline__ void st_stream(T* p, T v) {
-  __builtin_nontemporal_store(v, p);
+template <int VEC>
+__device__ __forceinline__ void st_stream(float* p, typename Vec<VEC>::type v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<typename Vec<VEC>::mem*>(p));
 }
 
 // Number of finished-row loads a thread keeps in flight before summing them.
 constexpr int kChunk = 16;
 
-// Sum of the finished rows of learner p at vector column v.  Rows are loaded
+// Sum of the finished rows of learner p at columns col .. col + VEC - 1.  Rows are loaded
 // kChunk at a time (the tail chunk predicated on the uniform count) so each
 // wave has kChunk independent 64 x VEC x 4-byte loads in flight.
 template <int VEC>
-__device__ __forceinline__ typename Vec<VEC>::type finished_sum(const typename Vec<VEC>::type* G,
-                                                                const Learners& L, int p, int m,
-                                                                int64_t pv, int64_t v) {
+__device__ __forceinline__ typename Vec<VEC>::type finished_sum(const float* G, const Learners& L,
+                                                                int p, int m, int64_t P,
+                                                                int64_t col) {
   using vf = typename Vec<VEC>::type;
-  const vf* g = G + (int64_t)p * m * pv + v;
+  const float* g = G + (int64_t)p * m * P + col;
   const int c = L.count[p];
   vf acc = (vf)(0.0f);
   for (int r = 0; r < c; r += kChunk) {
     vf a[kChunk];
 #pragma unroll
     for (int k = 0; k < kChunk; ++k)
-      a[k] = (r + k < c) ? ld_stream(g + (int64_t)row_of(L, p, r + k) * pv) : (vf)(0.0f);
+      a[k] = (r + k < c) ? ld_stream<VEC>(g + (int64_t)row_of(L, p, r + k) * P) : (vf)(0.0f);
 #pragma unroll
     for (int w = 1; w < kChunk; w *= 2)
 #pragma unroll
@@ -150,25 +155,19 @@ __device__ __forceinline__ typename Vec<VEC>::type mix_all(const typename Vec<VE
 // and the new server model is x - (1/n) sum_p eta_p v_p.
 constexpr int kServer = 2;
 
+// One tile of the step: columns col .. col + VEC - 1 of each lane, those below P
+// (a lane's columns are all below P or all beyond).
 template <int VEC, int ORDER>
-__global__ void __launch_bounds__(kStepBlock)
-    k_step(float* __restrict__ Xf, float* __restrict__ Vf, const float* __restrict__ Gf,
-           int64_t pv, int64_t ldv, int n, float mu, StepPlan S, Mixing W) {
+__device__ __forceinline__ void step_tile(float* __restrict__ X, float* __restrict__ V,
+                                          const float* __restrict__ G, int64_t col, int64_t P,
+                                          int64_t ld, int n, float mu, const StepPlan& S,
+                                          const Mixing& W, char* smem) {
   using vf = typename Vec<VEC>::type;
-  extern __shared__ char smem[];
   vf* zs = reinterpret_cast<vf*>(smem);        // [n][64]: values to be mixed
   vf* part = zs + n * kWave;                   // [runs][64]: partial row sums
-  vf* X = reinterpret_cast<vf*>(Xf);
-  vf* V = reinterpret_cast<vf*>(Vf);
-  const vf* G = reinterpret_cast<const vf*>(Gf);
-
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  // tiles in decreasing column order: gradient rows written just before in
-  // increasing column order (the MLP gradient kernels) are read newest first,
-  // while the memory-side cache may still hold them
-  const int64_t v = (int64_t)(gridDim.x - 1 - blockIdx.x) * kWave + lane;
-  const bool live = v < pv;
+  const bool live = col < P;
 
   // phase 1: own learners' X and V, and this wave's share of the G rows
   vf xo[kStepSlots], vo[kStepSlots];
@@ -178,8 +177,8 @@ __global__ void __launch_bounds__(kStepBlock)
     xo[s] = (vf)(0.0f);
     vo[s] = (vf)(0.0f);
     if (p < n && live) {
-      if (ORDER != kServer || p == 0) xo[s] = ld_stream(X + (int64_t)p * ldv + v);
-      vo[s] = ld_stream(V + (int64_t)p * ldv + v);
+      if (ORDER != kServer || p == 0) xo[s] = ld_stream<VEC>(X + (int64_t)p * ld + col);
+      vo[s] = ld_stream<VEC>(V + (int64_t)p * ld + col);
     }
   }
   const int e_end = S.seg[wave + 1];
@@ -193,7 +192,7 @@ __global__ void __launch_bounds__(kStepBlock)
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
       const int64_t row = (e + k < e_end) ? (int64_t)half_of(S.row, e + k) : 0;  // uniform
-      a[k] = (e + k < e_end && live) ? ld_stream(G + row * ldv + v) : (vf)(0.0f);
+      a[k] = (e + k < e_end && live) ? ld_stream<VEC>(G + row * ld + col) : (vf)(0.0f);
     }
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
@@ -223,7 +222,7 @@ __global__ void __launch_bounds__(kStepBlock)
       vf g = (vf)(0.0f);
       for (int r = S.lslot[q]; r < S.lslot[q + 1]; ++r) g += part[r * kWave + lane];
       const vf vn = mu * vo[s] + g * S.inv_c[q];
-      if (live) st_stream(V + (int64_t)q * ldv + v, vn);
+      if (live) st_stream<VEC>(V + (int64_t)q * ld + col, vn);
       if (ORDER == NBSGD_MIX_THEN_STEP) {
         zs[q * kWave + lane] = xo[s];
         keep[s] = S.eta[q] * vn;
@@ -238,7 +237,7 @@ __global__ void __launch_bounds__(kStepBlock)
 
   // phase 3: mix and write the new replicas (the server row: wave 0 only)
   if (ORDER == kServer) {
-    if (wave == 0 && live) st_stream(X + v, xo[0] - mix_all<VEC>(zs, kWave, n, lane) * W.w_all);
+    if (wave == 0 && live) st_stream<VEC>(X + col, xo[0] - mix_all<VEC>(zs, kWave, n, lane) * W.w_all);
     return;
   }
   vf total = (vf)(0.0f);
@@ -249,69 +248,103 @@ __global__ void __launch_bounds__(kStepBlock)
     if (i < n && live) {
       vf x = W.uniform ? total : mix_row<VEC>(zs, kWave, W, i, lane);
       if (ORDER == NBSGD_MIX_THEN_STEP) x -= keep[s];
-      st_stream(X + (int64_t)i * ldv + v, x);
+      st_stream<VEC>(X + (int64_t)i * ld + col, x);
     }
   }
 }
 
+template <int ORDER, bool EVEN>
+__global__ void __launch_bounds__(kStepBlock)
+    k_step(float* __restrict__ X, float* __restrict__ V, const float* __restrict__ G, int64_t P,
+           int64_t ld, int n, float mu, StepPlan S, Mixing W) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const Cols c = columns<EVEN, kWave>(gridDim.x - 1 - tile_of<EVEN>(blockIdx.x, gridDim.x),
+                                      threadIdx.x & (kWave - 1), P);
+  // tiles in decreasing column order: gradient rows written just before in
+  // increasing column order (the MLP gradient kernels) are read newest first,
+  // while the memory-side cache may still hold them
+  if (EVEN || c.vec4)
+    step_tile<4, ORDER>(X, V, G, c.col, P, ld, n, mu, S, W, smem);
+  else
+    step_tile<1, ORDER>(X, V, G, c.col, P, ld, n, mu, S, W, smem);
+}
+
 // Gbar[p] = (1/c_p) * sum of the finished rows of G[p]; blockIdx.y = learner.
 template <int VEC>
-__global__ void __launch_bounds__(kBlock)
-    k_accumulate(const float* __restrict__ Gf, float* __restrict__ Of, int64_t pv, int m,
-                 Learners L) {
-  using vf = typename Vec<VEC>::type;
+__device__ __forceinline__ void accumulate_cols(const float* __restrict__ G, float* __restrict__ O,
+                                                int64_t col, int64_t P, int m, const Learners& L) {
   const int p = blockIdx.y;
-  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (v >= pv) return;
-  const vf g = finished_sum<VEC>(reinterpret_cast<const vf*>(Gf), L, p, m, pv, v);
-  st_stream(reinterpret_cast<vf*>(Of) + (int64_t)p * pv + v, g * L.inv_c[p]);
+  if (col >= P) return;
+  st_stream<VEC>(O + (int64_t)p * P + col, finished_sum<VEC>(G, L, p, m, P, col) * L.inv_c[p]);
+}
+
+template <bool EVEN>
+__global__ void __launch_bounds__(kBlock)
+    k_accumulate(const float* __restrict__ G, float* __restrict__ O, int64_t P, int m, Learners L) {
+  const Cols c = columns<EVEN, kBlock>(blockIdx.x, threadIdx.x, P);
+  if (EVEN || c.vec4)
+    accumulate_cols<4>(G, O, c.col, P, m, L);
+  else
+    accumulate_cols<1>(G, O, c.col, P, m, L);
 }
 
 // V[p] = mu V[p] + Gbar[p]; X[p] -= eta_p V[p]; blockIdx.y = learner.
 template <int VEC>
-__global__ void __launch_bounds__(kBlock)
-    k_update(float* __restrict__ Xf, float* __restrict__ Vf, const float* __restrict__ Bf,
-             int64_t pv, float mu, Learners L) {
+__device__ __forceinline__ void update_cols(float* __restrict__ X, float* __restrict__ V,
+                                            const float* __restrict__ B, int64_t col, int64_t P,
+                                            float mu, const Learners& L) {
   using vf = typename Vec<VEC>::type;
   const int p = blockIdx.y;
-  const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (v >= pv) return;
-  const int64_t off = (int64_t)p * pv + v;
-  vf* X = reinterpret_cast<vf*>(Xf);
-  vf* V = reinterpret_cast<vf*>(Vf);
-  const vf vn = mu * ld_stream(V + off) + ld_stream(reinterpret_cast<const vf*>(Bf) + off);
-  st_stream(V + off, vn);
-  st_stream(X + off, ld_stream(X + off) - L.eta[p] * vn);
+  if (col >= P) return;
+  const int64_t off = (int64_t)p * P + col;
+  const vf vn = mu * ld_stream<VEC>(V + off) + ld_stream<VEC>(B + off);
+  st_stream<VEC>(V + off, vn);
+  st_stream<VEC>(X + off, ld_stream<VEC>(X + off) - L.eta[p] * vn);
 }
 
-// Y = W X through an LDS tile of all n rows; Y may equal X.
-template <int VEC>
+template <bool EVEN>
 __global__ void __launch_bounds__(kBlock)
-    k_mix(const float* Xf, float* Yf, int64_t pv, int n, Mixing W) {
+    k_update(float* __restrict__ X, float* __restrict__ V, const float* __restrict__ B, int64_t P,
+             float mu, Learners L) {
+  const Cols c = columns<EVEN, kBlock>(blockIdx.x, threadIdx.x, P);
+  if (EVEN || c.vec4)
+    update_cols<4>(X, V, B, c.col, P, mu, L);
+  else
+    update_cols<1>(X, V, B, c.col, P, mu, L);
+}
+
+// One tile of Y = W X through an LDS tile of all n rows; Y may equal X.
+template <int VEC>
+__device__ __forceinline__ void mix_tile(const float* X, float* Y, int64_t col, int64_t P, int n,
+                                         const Mixing& W, char* smem) {
   using vf = typename Vec<VEC>::type;
-  extern __shared__ char smem[];
   vf* zs = reinterpret_cast<vf*>(smem);
-  constexpr int ncols = kWave;
-  const vf* X = reinterpret_cast<const vf*>(Xf);
-  vf* Y = reinterpret_cast<vf*>(Yf);
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int64_t v = (int64_t)blockIdx.x * ncols + lane;
   for (int p = wave; p < n; p += kWaves)
-    if (v < pv) zs[p * ncols + lane] = ld_stream(X + (int64_t)p * pv + v);
+    if (col < P) zs[p * kWave + lane] = ld_stream<VEC>(X + (int64_t)p * P + col);
   __syncthreads();
-  if (v >= pv) return;
+  if (col >= P) return;
   vf total = (vf)(0.0f);
-  if (W.uniform) total = mix_all<VEC>(zs, ncols, n, lane) * W.w_all;
+  if (W.uniform) total = mix_all<VEC>(zs, kWave, n, lane) * W.w_all;
   for (int i = wave; i < n; i += kWaves) {
-    const vf y = W.uniform ? total : mix_row<VEC>(zs, ncols, W, i, lane);
-    st_stream(Y + (int64_t)i * pv + v, y);
+    const vf y = W.uniform ? total : mix_row<VEC>(zs, kWave, W, i, lane);
+    st_stream<VEC>(Y + (int64_t)i * P + col, y);
   }
 }
 
-// ------------------------------------------------------------------ host
+template <bool EVEN>
+__global__ void __launch_bounds__(kBlock) k_mix(const float* X, float* Y, int64_t P, int n, Mixing W) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const Cols c = columns<EVEN, kWave>(tile_of<EVEN>(blockIdx.x, gridDim.x),
+                                      threadIdx.x & (kWave - 1), P);
+  if (EVEN || c.vec4)
+    mix_tile<4>(X, Y, c.col, P, n, W, smem);
+  else
+    mix_tile<1>(X, Y, c.col, P, n, W, smem);
+}
 
-int vec_width(int64_t P) { return (P % 4 == 0) ? 4 : (P % 2 == 0) ? 2 : 1; }
+// ------------------------------------------------------------------ host
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
@@ -334,13 +367,14 @@ nbsgd_status check_rows(const void* p, const char* name) {
 
 static_assert(sizeof(StepPlan) + sizeof(Mixing) + 64 <= 4096, "kernel arguments exceed 4 KiB");
 
-template <int VEC, int ORDER>
-void launch_step(float* X, float* V, const float* G, int64_t pv, int64_t ldv, int n, float mu,
+template <int ORDER>
+void launch_step(float* X, float* V, const float* G, int64_t P, int64_t ld, int n, float mu,
                  const StepPlan& S, int runs, const Mixing& W, hipStream_t s) {
-  const int64_t blocks = (pv + kWave - 1) / kWave;
-  const size_t lds = (size_t)(n + runs) * kWave * VEC * sizeof(float);
-  hipLaunchKernelGGL((k_step<VEC, ORDER>), dim3((unsigned)blocks), dim3(kStepBlock), lds, s, X,
-                     V, G, pv, ldv, n, mu, S, W);
+  const size_t lds = (size_t)(n + runs) * 4 * kWave * sizeof(float);
+  const bool ev = even_rows(P, ld);
+  hipLaunchKernelGGL((ev ? k_step<ORDER, true> : k_step<ORDER, false>),
+                     dim3((unsigned)tiles<kWave>(P, ev)), dim3(kStepBlock), lds, s, X, V, G, P, ld,
+                     n, mu, S, W);
 }
 
 // The fused step on rows `ld` floats apart (ld >= P).
@@ -366,20 +400,13 @@ nbsgd_status step_impl(float* X, float* V, const float* G, int64_t ld, const uin
   if (overlap(X, xb, V, xb)) return fail(NBSGD_E_ARG, "X and V overlap");
   if (overlap(G, gb, X, xb) || overlap(G, gb, V, xb))
     return fail(NBSGD_E_ARG, "G overlaps X or V");
-  const int vec = std::min(vec_width(P), vec_width(ld));  // divides both P and ld
-  const int64_t pv = P / vec, ldv = ld / vec;
-  if ((pv + kWave - 1) / kWave > 0x7fffffff)
+  if (tiles<kWave>(P, false) > 0x7fffffff)
     return fail(NBSGD_E_UNSUPPORTED, "P=%lld needs too many workgroups", (long long)P);
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (order == NBSGD_MIX_THEN_STEP) {
-    if (vec == 4) launch_step<4, NBSGD_MIX_THEN_STEP>(X, V, G, pv, ldv, n, momentum, S, runs, W, s);
-    else if (vec == 2) launch_step<2, NBSGD_MIX_THEN_STEP>(X, V, G, pv, ldv, n, momentum, S, runs, W, s);
-    else launch_step<1, NBSGD_MIX_THEN_STEP>(X, V, G, pv, ldv, n, momentum, S, runs, W, s);
-  } else {
-    if (vec == 4) launch_step<4, NBSGD_STEP_THEN_MIX>(X, V, G, pv, ldv, n, momentum, S, runs, W, s);
-    else if (vec == 2) launch_step<2, NBSGD_STEP_THEN_MIX>(X, V, G, pv, ldv, n, momentum, S, runs, W, s);
-    else launch_step<1, NBSGD_STEP_THEN_MIX>(X, V, G, pv, ldv, n, momentum, S, runs, W, s);
-  }
+  if (order == NBSGD_MIX_THEN_STEP)
+    launch_step<NBSGD_MIX_THEN_STEP>(X, V, G, P, ld, n, momentum, S, runs, W, s);
+  else
+    launch_step<NBSGD_STEP_THEN_MIX>(X, V, G, P, ld, n, momentum, S, runs, W, s);
   return check_launch("nbsgd_step");
 }
 
@@ -421,15 +448,10 @@ extern "C" nbsgd_status nbsgd_step_server(float* x, float* V, const float* G, in
   const int64_t vb = ((int64_t)(n - 1) * ld + P) * 4, gb = ((int64_t)n * m - 1) * ld * 4 + P * 4;
   if (overlap(x, P * 4, V, vb)) return fail(NBSGD_E_ARG, "x and V overlap");
   if (overlap(G, gb, x, P * 4) || overlap(G, gb, V, vb)) return fail(NBSGD_E_ARG, "G overlaps x or V");
-  const int vec = std::min(vec_width(P), vec_width(ld));
-  const int64_t pv = P / vec, ldv = ld / vec;
-  if ((pv + kWave - 1) / kWave > 0x7fffffff)
+  if (tiles<kWave>(P, false) > 0x7fffffff)
     return fail(NBSGD_E_UNSUPPORTED, "P=%lld needs too many workgroups", (long long)P);
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   // x is a single row: the kernel reads and writes row 0 only
-  if (vec == 4) launch_step<4, kServer>(x, V, G, pv, ldv, n, momentum, S, runs, W, s);
-  else if (vec == 2) launch_step<2, kServer>(x, V, G, pv, ldv, n, momentum, S, runs, W, s);
-  else launch_step<1, kServer>(x, V, G, pv, ldv, n, momentum, S, runs, W, s);
+  launch_step<kServer>(x, V, G, P, ld, n, momentum, S, runs, W, reinterpret_cast<hipStream_t>(stream));
   return check_launch("nbsgd_step_server");
 }
 
@@ -445,15 +467,10 @@ extern "C" nbsgd_status nbsgd_accumulate(const float* G, const uint8_t* mask, in
   if (nbsgd_status st = check_rows(Gbar, "Gbar")) return st;
   if (overlap(G, (int64_t)n * m * P * 4, Gbar, (int64_t)n * P * 4))
     return fail(NBSGD_E_ARG, "G and Gbar overlap");
-  const int vec = vec_width(P);
-  const int64_t pv = P / vec;
-  const int64_t blocks = (pv + kBlock - 1) / kBlock;
-  if (blocks > 0x7fffffff) return fail(NBSGD_E_UNSUPPORTED, "P too large");
-  const dim3 grid((unsigned)blocks, (unsigned)n);
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (vec == 4) hipLaunchKernelGGL(k_accumulate<4>, grid, dim3(kBlock), 0, s, G, Gbar, pv, m, L);
-  else if (vec == 2) hipLaunchKernelGGL(k_accumulate<2>, grid, dim3(kBlock), 0, s, G, Gbar, pv, m, L);
-  else hipLaunchKernelGGL(k_accumulate<1>, grid, dim3(kBlock), 0, s, G, Gbar, pv, m, L);
+  if (tiles<kBlock>(P, false) > 0x7fffffff) return fail(NBSGD_E_UNSUPPORTED, "P too large");
+  const bool ev = even_rows(P, P);
+  hipLaunchKernelGGL((ev ? k_accumulate<true> : k_accumulate<false>), dim3((unsigned)tiles<kBlock>(P, ev), (unsigned)n),
+                     dim3(kBlock), 0, reinterpret_cast<hipStream_t>(stream), G, Gbar, P, m, L);
   return check_launch("nbsgd_accumulate");
 }
 
@@ -478,15 +495,10 @@ extern "C" nbsgd_status nbsgd_update(float* X, float* V, const float* Gbar, cons
   const int64_t xb = (int64_t)n * P * 4;
   if (overlap(X, xb, V, xb) || overlap(X, xb, Gbar, xb) || overlap(V, xb, Gbar, xb))
     return fail(NBSGD_E_ARG, "X, V and Gbar must not overlap");
-  const int vec = vec_width(P);
-  const int64_t pv = P / vec;
-  const int64_t blocks = (pv + kBlock - 1) / kBlock;
-  if (blocks > 0x7fffffff) return fail(NBSGD_E_UNSUPPORTED, "P too large");
-  const dim3 grid((unsigned)blocks, (unsigned)n);
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (vec == 4) hipLaunchKernelGGL(k_update<4>, grid, dim3(kBlock), 0, s, X, V, Gbar, pv, momentum, L);
-  else if (vec == 2) hipLaunchKernelGGL(k_update<2>, grid, dim3(kBlock), 0, s, X, V, Gbar, pv, momentum, L);
-  else hipLaunchKernelGGL(k_update<1>, grid, dim3(kBlock), 0, s, X, V, Gbar, pv, momentum, L);
+  if (tiles<kBlock>(P, false) > 0x7fffffff) return fail(NBSGD_E_UNSUPPORTED, "P too large");
+  const bool ev = even_rows(P, P);
+  hipLaunchKernelGGL((ev ? k_update<true> : k_update<false>), dim3((unsigned)tiles<kBlock>(P, ev), (unsigned)n),
+                     dim3(kBlock), 0, reinterpret_cast<hipStream_t>(stream), X, V, Gbar, P, momentum, L);
   return check_launch("nbsgd_update");
 }
 
@@ -502,14 +514,10 @@ extern "C" nbsgd_status nbsgd_mix(const float* X, const float* Wh, int32_t n, in
   if (nbsgd_status st = check_rows(Y, "Y")) return st;
   const int64_t xb = (int64_t)n * P * 4;
   if (X != Y && overlap(X, xb, Y, xb)) return fail(NBSGD_E_ARG, "X and Y partially overlap");
-  const int vec = vec_width(P);
-  const int64_t pv = P / vec;
-  const int64_t blocks = (pv + kWave - 1) / kWave;
-  if (blocks > 0x7fffffff) return fail(NBSGD_E_UNSUPPORTED, "P too large");
-  const size_t lds = (size_t)n * kWave * vec * sizeof(float);
-  hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  if (vec == 4) hipLaunchKernelGGL(k_mix<4>, dim3((unsigned)blocks), dim3(kBlock), lds, s, X, Y, pv, n, W);
-  else if (vec == 2) hipLaunchKernelGGL(k_mix<2>, dim3((unsigned)blocks), dim3(kBlock), lds, s, X, Y, pv, n, W);
-  else hipLaunchKernelGGL(k_mix<1>, dim3((unsigned)blocks), dim3(kBlock), lds, s, X, Y, pv, n, W);
+  if (tiles<kWave>(P, false) > 0x7fffffff) return fail(NBSGD_E_UNSUPPORTED, "P too large");
+  const size_t lds = (size_t)n * 4 * kWave * sizeof(float);
+  const bool ev = even_rows(P, P);
+  hipLaunchKernelGGL((ev ? k_mix<true> : k_mix<false>), dim3((unsigned)tiles<kWave>(P, ev)),
+                     dim3(kBlock), lds, reinterpret_cast<hipStream_t>(stream), X, Y, P, n, W);
   return check_launch("nbsgd_mix");
 }
