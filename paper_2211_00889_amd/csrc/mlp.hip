@@ -36,8 +36,11 @@ using namespace nbsgd;
 
 namespace {
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
 
 // kBatch, kMaxHidden, kMaxClasses, kFeatBlock, kSkMaxSlices and Dims: mlp_shape.h
 constexpr int kMaxList = 896;    // mini-batches per launch group (kernel-argument list)
@@ -82,12 +85,16 @@ __device__ __forceinline__ int item_slot(uint32_t w) { return (int)((w >> 12) & 
 
 __device__ __forceinline__ float bf16r(float x) { return (float)(__bf16)x; }
 
+// Two (eight) floats to bf16 as one vector conversion: one v_cvt_pk_bf16_f32 a
+// pair.  Converted one by one and combined by hand they took seven instructions a
+// pair, and the conversions, not the matrix cores or the loads, filled the VALUs of
+// the forward (70% busy on 4,096 samples).
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-  const __bf16 a = (__bf16)lo, b = (__bf16)hi;
-  uint16_t ua, ub;
-  __builtin_memcpy(&ua, &a, 2);
-  __builtin_memcpy(&ub, &b, 2);
-  return (uint32_t)ua | ((uint32_t)ub << 16);
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
+}
+__device__ __forceinline__ bf16x8 to_bf16(f32x4 lo, f32x4 hi) {
+  return __builtin_convertvector((f32x8){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]},
+                                 bf16x8);
 }
 
 // Writes the sample index of every row of the chunk's list entries (used
@@ -111,7 +118,9 @@ __global__ void __launch_bounds__(256) k_put_idx(int32_t* __restrict__ dst, IdxC
 // partial sums go to slice s of the partial buffer; k_mlp_head adds the
 // slices in slice order.  The work items are split into eight equal ranges,
 // one per XCD (workgroup b runs on XCD b % 8), so the items of one learner
-// share an L2.  INLINE: the sample indices come from the kernel arguments and
+// share an L2; the unit blocks of a quad's slice follow each other, so that they
+// read its sample rows at the same time (4,096 samples: 200 MB of reads past the
+// L2s with the unit blocks a round apart, 75 MB so, 57.5 -> 55.1 us).  INLINE: the sample indices come from the kernel arguments and
 // the workgroups of slice 0 and unit block 0 copy them to the workspace for
 // the later kernels; otherwise they are read from the workspace.
 constexpr int kSkRows = 128, kSkUnits = 128, kSkKc = 64, kSkLdA = kSkKc, kSkLdW = kSkKc + 16;
@@ -144,9 +153,9 @@ __global__ void __launch_bounds__(512)
   const int cnt = M.first[li + 1] - M.first[li];
   const int quads = (cnt + 3) >> 2;
   int local = g - M.off[li];
-  const int quad = local % quads;
-  local /= quads;
-  const int ubk = local % M.ub, s = local / M.ub;
+  const int ubk = local % M.ub;
+  local /= M.ub;
+  const int quad = local % quads, s = local / quads;
   const int e0 = M.first[li] + 4 * quad;         // first list entry of the quad
   const int nmb = min(4, cnt - 4 * quad);
   const int rows = kBatch * nmb;
@@ -159,7 +168,7 @@ __global__ void __launch_bounds__(512)
   const float* prm = X + (int64_t)learner * d.ld;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wr = wave & 3, wu = wave >> 2;
-  const bool mma = 32 * wr < rows && 64 * wu < units;  // wave-uniform
+  const bool mma = 32 * wr < rows && 64 * wu < units;  // anything to store (wave-uniform)
 
   // A staging: wave w takes rows 16 w .. +15, four consecutive lanes per row
   // (64 contiguous bytes, k = 4 q + 16 j + 0..3); the four rows of a 16-lane
@@ -168,9 +177,9 @@ __global__ void __launch_bounds__(512)
   const int aquad = lane >> 2, aq = lane & 3;
   const int arow = 16 * wave + ((aquad >> 2) & 1) + 2 * (aquad & 3) + 8 * (aquad >> 3);
   // Rows past the tile's mini-batches read sample 0 and unit quads past the
-  // block read its first units (both in bounds); stage() masks them to
-  // zero.  The loads are unconditional, so the compiler can wait for one
-  // register set while the next is still in flight.
+  // block read its first units (both in bounds); what they give is a row or
+  // column of the product that nothing stores.  The loads are unconditional, so
+  // the compiler can wait for one register set while the next is in flight.
   const bool alive = arow < rows;
   const float* asrc = data + kb + 4 * aq;
   if (alive) {
@@ -190,8 +199,6 @@ __global__ void __launch_bounds__(512)
   const int wa = 2 * wave + ((lane >> 2) & 1), wq = 4 * (lane >> 3) + (lane & 3);
   const bool wlive = 4 * wq < units;
   const float* wsrc = prm + (int64_t)(kb + 4 * wa) * H + u0 + 4 * (wlive ? wq : 0);
-  // masks rather than selects, so the staging has no branches either
-  const uint32_t amask = alive ? ~0u : 0u, wmask = wlive ? ~0u : 0u;
 
   struct Regs {
     f32x4 a[4], w[4];
@@ -208,14 +215,14 @@ __global__ void __launch_bounds__(512)
     __bf16* a = As[buf] + arow * kSkLdA + 4 * (aq & 1);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const uint2 v = {pack_bf16(R.a[j][0], R.a[j][1]) & amask, pack_bf16(R.a[j][2], R.a[j][3]) & amask};
+      const uint2 v = {pack_bf16(R.a[j][0], R.a[j][1]), pack_bf16(R.a[j][2], R.a[j][3])};
       *reinterpret_cast<uint2*>(a + 8 * (((aq >> 1) + 2 * j) ^ (arow & 7))) = v;
     }
     // units 4 wq + t, k-quad wa: half wa % 2 of octet wa / 2, swizzled by wq % 8
     __bf16* w = Ws[buf] + (4 * wq) * kSkLdW + 8 * ((wa >> 1) ^ (wq & 7)) + 4 * (wa & 1);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const uint2 v = {pack_bf16(R.w[0][t], R.w[1][t]) & wmask, pack_bf16(R.w[2][t], R.w[3][t]) & wmask};
+      const uint2 v = {pack_bf16(R.w[0][t], R.w[1][t]), pack_bf16(R.w[2][t], R.w[3][t])};
       *reinterpret_cast<uint2*>(w + t * kSkLdW) = v;
     }
   };
@@ -225,7 +232,6 @@ __global__ void __launch_bounds__(512)
 #pragma unroll
     for (int u = 0; u < 4; ++u) acc[f][u] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto multiply = [&](int buf) {
-    if (!mma) return;
     // lane: row or unit l % 16 of the fragment, octet 4 ks + l / 16 (swizzled)
     const int g = lane >> 4;
     const __bf16* a = As[buf] + (32 * wr + (lane & 15)) * kSkLdA;
