@@ -5,9 +5,9 @@
 //
 // Every GEMM input is rounded to bf16 (round to nearest even, the hardware
 // conversion) and multiplied with fp32 accumulation:
-//   k_mlp_fwd_sk  partial Z1 = A W1 over one slice of d_in, per 128-row x
-//                 128-unit tile, on MFMA 16x16x32 (both operands staged in LDS)
-//   k_mlp_head    per mini-batch: Z1 = sum of the slices + b1, H =
+//   k_mlp_fwd    partial Z1 = A W1 over one slice of d_in, per 128-row x
+//                128-unit tile, on MFMA 16x16x32 (both operands staged in LDS)
+//   k_mlp_head   per mini-batch: Z1 = sum of the slices + b1, H =
 //                 bf16(relu(Z1)), logits = H W2 + b2 (MFMA, classes padded to
 //                 16), softmax-CE, dZ2; dZ1 = (dZ2 W2^T) * [Z1 > 0], db1, dW2 =
 //                 H^T dZ2 (MFMA), db2 and the loss
@@ -107,23 +107,36 @@ __global__ void __launch_bounds__(256) k_put_idx(int32_t* __restrict__ dst, IdxC
 }
 
 // Forward, split over d_in.  Work item: a quad (up to four mini-batches of one
-// learner, 128 rows), a block of 128 hidden units and one of S equal slices of
-// d_in (S = the largest divisor of d_in / 64 up to kSkMaxSlices).  Both operands
-// are staged through LDS in bf16 ([row][k] and [unit][k]), so a 16-byte read
-// is one MFMA fragment; the 16-byte k-octets of a row are XOR-swizzled so
-// that the fragment reads and the staging writes are free of bank conflicts
-// on gfx950 (A: 64 bf16 per row, octet o at o ^ (row % 8); W1: 80 bf16 per
-// row, octet o at o ^ (unit / 4 % 8)).  Eight waves: wave w takes rows
-// 32 (w % 4) .. +31 and units 64 (w / 4) .. +63 (2 x 4 accumulators).  The
-// partial sums go to slice s of the partial buffer; k_mlp_head adds the
-// slices in slice order.  The work items are split into eight equal ranges,
-// one per XCD (workgroup b runs on XCD b % 8), so the items of one learner
-// share an L2; the unit blocks of a quad's slice follow each other, so that they
-// read its sample rows at the same time (4,096 samples: 200 MB of reads past the
-// L2s with the unit blocks a round apart, 75 MB so, 57.5 -> 55.1 us).  INLINE: the sample indices come from the kernel arguments and
-// the workgroups of slice 0 and unit block 0 copy them to the workspace for
+// learner, 128 rows), a block of 128 hidden units and one of S slices of d_in (in
+// chunks of 64, as equal as they go).  Eight waves: wave w takes all 128 units for mini-batch w % 4 over half
+// w / 4 of the slice (2 x 8 accumulators), so that a W1 fragment read from LDS
+// feeds two MFMAs and four waves share its staging.  Per chunk of 64 k:
+//   W1  [half][unit][k] in bf16, staged by all waves for all (each thread
+//       transposes a 4 k x 4 unit cell of either half), two buffers, one barrier
+//       a chunk; loaded one chunk ahead of its staging
+//   A   the wave's own 32 rows, loaded one chunk ahead with four lanes on 64
+//       contiguous bytes of a row, converted into the wave's own LDS rows and read
+//       back as fragments: no other wave needs them, so no barrier.  (Loading the
+//       fragments straight from memory puts the 16 rows of a tile on consecutive
+//       lanes, and the L1 then serves 16 bytes an access: 36.6 against 28.7 us.)
+// Rows are 64 bf16 (128 bytes); octet o of a row is stored at o ^ swizzle(row),
+// which leaves the 8-byte writes (16 lanes a cycle) and the 16-byte fragment reads
+// free of bank conflicts; a 64-unit group's unit 4 q + t is LDS row 16 t + q, so
+// that lane q of a result holds four consecutive units.  The two halves are added
+// through LDS at the end (first half + second half) and the sum goes to slice s
+// of the partial buffer; k_mlp_head adds the slices in slice order.
+// What bounds it: with samples and W1 cold (8 x 8 workload, 73 MB) their fetch, 27-33
+// us; with 4,096 samples of one learner the chunk's chain of staging, LDS reads and
+// MFMAs and the partial sums' write, 26 us (45.8 with 32-row x 64-unit waves,
+// both operands staged for all waves and 1/4 slices: twice the partial sums).
+// The work items are split into eight equal ranges, one per XCD (workgroup b runs
+// on XCD b % 8), so the items of one learner share an L2; the unit blocks of a
+// quad's slice follow each other, so that they read its sample rows at the same
+// time (4,096 samples: 200 MB of reads past the L2s with the unit blocks a round
+// apart, 75 MB so).  INLINE: the sample indices come from the kernel arguments
+// and the workgroups of slice 0 and unit block 0 copy them to the workspace for
 // the later kernels; otherwise they are read from the workspace.
-constexpr int kSkRows = 128, kSkUnits = 128, kSkKc = 64, kSkLdA = kSkKc, kSkLdW = kSkKc + 16;
+constexpr int kFwWaves = 8, kFwMb = 4, kFwUnits = 128, kFwKc = 64;
 struct SkMap {
   int32_t n;              // learners present
   int32_t S;              // K slices
@@ -136,166 +149,188 @@ static_assert(NBSGD_MAX_LEARNERS <= 16, "SkMap holds at most 16 learners");
 static_assert(sizeof(InlineIdx) + sizeof(Dims) + sizeof(SkMap) + 5 * 8 <= 4096,
               "kernel arguments exceed 4 KiB");
 
+// Orders the wave's LDS writes before its later LDS accesses (other lanes' data).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Swizzle of row r of a 16-row tile: within rows 0-7 and within 8-15 all eight
+// values differ (writes), and so they do within the even and the odd rows, in
+// pairs 2 v, 2 v + 1 for rows 0-3 and 12-15 (reads).
+__device__ __forceinline__ int fwd_swizzle(int r) {
+  return ((r & 4) | (r & 1) << 1 | ((r >> 1) & 1)) ^ (r & 8 ? 6 : 0);
+}
+
 template <bool INLINE>
-__global__ void __launch_bounds__(512)
-    k_mlp_fwd_sk(const float* __restrict__ X, const float* __restrict__ data,
-                 int32_t* __restrict__ idx, float* __restrict__ Zpart, int64_t part_stride, Dims d,
-                 SkMap M, Idx16<INLINE ? kInline * kBatch / 2 : 1> I) {
-  constexpr int kDepth = 2;  // chunks loaded ahead of the one being staged
-  __shared__ __attribute__((aligned(16))) __bf16 As[2][kSkRows * kSkLdA];
-  __shared__ __attribute__((aligned(16))) __bf16 Ws[2][kSkUnits * kSkLdW];
+__global__ void __launch_bounds__(64 * kFwWaves, 2)
+    k_mlp_fwd(const float* __restrict__ X, const float* __restrict__ data,
+              int32_t* __restrict__ idx, float* __restrict__ Zpart, int64_t part_stride, Dims d,
+              SkMap M, Idx16<INLINE ? kInline * kBatch / 2 : 1> I) {
+  constexpr int UB = kFwUnits, KC = kFwKc;
+  __shared__ __attribute__((aligned(16))) __bf16 Ws[2][2][UB * KC];
+  __shared__ __attribute__((aligned(16))) __bf16 As[kFwWaves][kBatch * KC];
   const int xcd = blockIdx.x & 7;
   const int64_t total = M.off[M.n];
-  const int g = (int)(xcd * total / 8) + (int)(blockIdx.x >> 3);
-  if (g >= (int)((xcd + 1) * total / 8)) return;  // uniform
+  const int item = (int)(xcd * total / 8) + (int)(blockIdx.x >> 3);
+  if (item >= (int)((xcd + 1) * total / 8)) return;  // uniform
   int li = 0;
-  while (li + 1 < M.n && M.off[li + 1] <= g) ++li;
+  while (li + 1 < M.n && M.off[li + 1] <= item) ++li;
   const int cnt = M.first[li + 1] - M.first[li];
-  const int quads = (cnt + 3) >> 2;
-  int local = g - M.off[li];
+  const int quads = (cnt + kFwMb - 1) / kFwMb;
+  int local = item - M.off[li];
   const int ubk = local % M.ub;
   local /= M.ub;
   const int quad = local % quads, s = local / quads;
-  const int e0 = M.first[li] + 4 * quad;         // first list entry of the quad
-  const int nmb = min(4, cnt - 4 * quad);
-  const int rows = kBatch * nmb;
-  const int H = d.hidden;
-  const int u0 = kSkUnits * ubk;
-  const int units = min(kSkUnits, H - u0);
-  const int kslice = d.d_in / M.S, nck = kslice / kSkKc;
-  const int kb = s * kslice;
+  const int e0 = M.first[li] + kFwMb * quad;  // first list entry of the quad
+  const int nmb = min(kFwMb, cnt - kFwMb * quad);
+  const int H = d.hidden, u0 = UB * ubk;
+  const int units = min(UB, H - u0);
+  // chunks of the slice's halves: [kc[0], kc[1]) and [kc[1], kc[2])
+  const int T = d.d_in / KC;
+  const int kc[3] = {2 * s * T / (2 * M.S), (2 * s + 1) * T / (2 * M.S), (2 * s + 2) * T / (2 * M.S)};
+  const int n0 = kc[1] - kc[0], n1 = kc[2] - kc[1];
+  const int nck = max(n0, n1), nmin = min(n0, n1);  // they differ by at most one
   const int learner = (int)((M.learner[li >> 2] >> (8 * (li & 3))) & 0xffu);
-  const float* prm = X + (int64_t)learner * d.ld;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave & 3, wu = wave >> 2;
-  const bool mma = 32 * wr < rows && 64 * wu < units;  // anything to store (wave-uniform)
-
-  // A staging: wave w takes rows 16 w .. +15, four consecutive lanes per row
-  // (64 contiguous bytes, k = 4 q + 16 j + 0..3); the four rows of a 16-lane
-  // group are two apart, which with the swizzle spreads its writes over all
-  // banks.
-  const int aquad = lane >> 2, aq = lane & 3;
-  const int arow = 16 * wave + ((aquad >> 2) & 1) + 2 * (aquad & 3) + 8 * (aquad >> 3);
-  // Rows past the tile's mini-batches read sample 0 and unit quads past the
-  // block read its first units (both in bounds); what they give is a row or
-  // column of the product that nothing stores.  The loads are unconditional, so
-  // the compiler can wait for one register set while the next is in flight.
-  const bool alive = arow < rows;
-  const float* asrc = data + kb + 4 * aq;
-  if (alive) {
-    const int t = e0 * kBatch + arow;  // workspace row: entry e0 + arow / 32, row arow % 32
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mb = wave & 3, kh = wave >> 2;
+  const int i = lane & 15, g = lane >> 4;
+  const bool live = mb < nmb;
+  // Mini-batches past the quad's read its first one and unit quads past the block
+  // its first units (both in bounds); nothing stores what they give.
+  // A: rows 16 f + ar, floats 4 p .. +3 of every 16
+  const int p = lane & 3, ar = ((lane >> 2) & 1) | ((lane >> 3) & 3) << 2 | (lane >> 5) << 1;
+  const float* ap[2];
+#pragma unroll
+  for (int f = 0; f < 2; ++f) {
+    const int t = (e0 + (live ? mb : 0)) * kBatch + 16 * f + ar;
     int32_t v;
     if constexpr (INLINE) {
       v = (int32_t)((I.v[t >> 1] >> (16 * (t & 1))) & 0xffffu);
-      if (s == 0 && ubk == 0 && aq == 0) idx[t] = v;
+      if (live && kh == 0 && s == 0 && ubk == 0 && p == 0) idx[t] = v;
     } else {
       v = idx[t];
     }
-    asrc = data + (int64_t)v * d.d_in + kb + 4 * aq;
+    ap[f] = data + (int64_t)v * d.d_in + kc[kh] * KC + 4 * p;
   }
-  // W1 staging: k rows 4 wa .. +3, units 4 wq .. +3; wave w takes the k-quads
-  // 2 w and 2 w + 1, four consecutive lanes read 64 contiguous bytes of one k
-  // row, and each load of the wave reads two whole 512-byte row pieces.
-  const int wa = 2 * wave + ((lane >> 2) & 1), wq = 4 * (lane >> 3) + (lane & 3);
-  const bool wlive = 4 * wq < units;
-  const float* wsrc = prm + (int64_t)(kb + 4 * wa) * H + u0 + 4 * (wlive ? wq : 0);
+  // W1: k 8 wave + 4 half .. +3 of either half's chunk, units 4 wq .. +3; four
+  // lanes read 64 contiguous bytes, a load two whole 512-byte row pieces
+  const int wq = 4 * (lane >> 3) + (lane & 3);
+  const int half = (lane >> 2) & 1;
+  const float* wp = X + (int64_t)learner * d.ld + (int64_t)(8 * wave + 4 * half) * H + u0 +
+                    (4 * wq < units ? 4 * wq : 0);
+  const int wofs = (64 * (wq >> 4) + (wq & 15)) * KC + 8 * (wave ^ fwd_swizzle(wq & 15)) + 4 * half;
 
-  struct Regs {
-    f32x4 a[4], w[4];
+  f32x4 a[2][KC / 16], w[2][4];
+  const int na = kh ? n1 : n0;  // this wave's chunks
+  auto load_a = [&](int c) {
+    c = min(c, na - 1);
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int q = 0; q < KC / 16; ++q) a[f][q] = *reinterpret_cast<const f32x4*>(ap[f] + c * KC + 16 * q);
   };
-  auto load = [&](Regs& R, int c) {
-    const int k0 = c * kSkKc;
+  auto load_w = [&](int c) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) R.a[j] = *reinterpret_cast<const f32x4*>(asrc + k0 + 16 * j);
+    for (int h = 0; h < 2; ++h) {
+      const int k = kc[h] + min(c, (h ? n1 : n0) - 1);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) R.w[r] = *reinterpret_cast<const f32x4*>(wsrc + (int64_t)(k0 + r) * H);
-  };
-  auto stage = [&](const Regs& R, int buf) {
-    // k-quad aq + 4 j is half aq % 2 of octet aq / 2 + 2 j
-    __bf16* a = As[buf] + arow * kSkLdA + 4 * (aq & 1);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint2 v = {pack_bf16(R.a[j][0], R.a[j][1]), pack_bf16(R.a[j][2], R.a[j][3])};
-      *reinterpret_cast<uint2*>(a + 8 * (((aq >> 1) + 2 * j) ^ (arow & 7))) = v;
-    }
-    // units 4 wq + t, k-quad wa: half wa % 2 of octet wa / 2, swizzled by wq % 8
-    __bf16* w = Ws[buf] + (4 * wq) * kSkLdW + 8 * ((wa >> 1) ^ (wq & 7)) + 4 * (wa & 1);
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const uint2 v = {pack_bf16(R.w[0][t], R.w[1][t]), pack_bf16(R.w[2][t], R.w[3][t])};
-      *reinterpret_cast<uint2*>(w + t * kSkLdW) = v;
+      for (int r = 0; r < 4; ++r) w[h][r] = *reinterpret_cast<const f32x4*>(wp + (int64_t)(k * KC + r) * H);
     }
   };
-  f32x4 acc[2][4];
+  auto stage_w = [&](int buf) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const uint2 v = {pack_bf16(w[h][0][t], w[h][1][t]), pack_bf16(w[h][2][t], w[h][3][t])};
+        *reinterpret_cast<uint2*>(&Ws[buf][h][wofs + 16 * t * KC]) = v;
+      }
+  };
+  __bf16* aw = As[wave];
+  auto stage_a = [&]() {
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int q = 0; q < KC / 16; ++q) {
+        const uint2 v = {pack_bf16(a[f][q][0], a[f][q][1]), pack_bf16(a[f][q][2], a[f][q][3])};
+        *reinterpret_cast<uint2*>(aw + (16 * f + ar) * KC + 8 * ((2 * q + (p >> 1)) ^ fwd_swizzle(ar)) + 4 * (p & 1)) = v;
+      }
+    wave_lds_fence();
+  };
+  f32x4 acc[2][UB / 16];
 #pragma unroll
   for (int f = 0; f < 2; ++f)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc[f][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int u = 0; u < UB / 16; ++u) acc[f][u] = f32x4{0.f, 0.f, 0.f, 0.f};
   auto multiply = [&](int buf) {
-    // lane: row or unit l % 16 of the fragment, octet 4 ks + l / 16 (swizzled)
-    const int g = lane >> 4;
-    const __bf16* a = As[buf] + (32 * wr + (lane & 15)) * kSkLdA;
-    const __bf16* w = Ws[buf] + (64 * wu + (lane & 15)) * kSkLdW;
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int oa = 8 * ((4 * ks + g) ^ (lane & 7));
-      bf16x8 fa[2];
+    for (int ks = 0; ks < KC / 32; ++ks) {
+      const int o = 8 * ((4 * ks + g) ^ fwd_swizzle(i));
+      const bf16x8 a0 = *reinterpret_cast<const bf16x8*>(aw + i * KC + o);
+      const bf16x8 a1 = *reinterpret_cast<const bf16x8*>(aw + (16 + i) * KC + o);
 #pragma unroll
-      for (int f = 0; f < 2; ++f)
-        fa[f] = *reinterpret_cast<const bf16x8*>(a + 16 * f * kSkLdA + oa);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int ow = 8 * ((4 * ks + g) ^ (4 * (u & 1) + ((lane >> 2) & 3)));
-        const bf16x8 fb = *reinterpret_cast<const bf16x8*>(w + 16 * u * kSkLdW + ow);
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-          acc[f][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[f], fb, acc[f][u], 0, 0, 0);
+      for (int u = 0; u < UB / 16; ++u) {
+        const bf16x8 b = *reinterpret_cast<const bf16x8*>(
+            &Ws[buf][kh][(64 * (u >> 2) + 16 * (u & 3) + i) * KC + o]);
+        acc[0][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a0, b, acc[0][u], 0, 0, 0);
+        acc[1][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a1, b, acc[1][u], 0, 0, 0);
       }
     }
+    wave_lds_fence();
   };
-  // prologue: chunks 0 .. kDepth (indices clamped to the last chunk, so the
-  // loads are unconditional and staging chunk 0 waits for its own loads only)
-  Regs R[kDepth];
-#pragma unroll
-  for (int c = 0; c < kDepth; ++c) load(R[c], min(c, nck - 1));
-  stage(R[0], 0);
-  load(R[0], min(kDepth, nck - 1));
+  // chunk indices past the last one are clamped, so that the loads stay
+  // unconditional; set c + 1 is loaded while chunk c is multiplied
+  load_w(0);
+  load_a(0);
+  stage_w(0);
+  load_w(1);
   __syncthreads();
-  // step c: multiply chunk c (buffer c % 2); stage chunk c+1 from its register
-  // set and refill that set with chunk c+1+kDepth
-  auto step = [&](int c, Regs& Rn) {
+  for (int c = 0; c < nmin; ++c) {
+    stage_a();
+    load_a(c + 1);
     multiply(c & 1);
-    if (c + 1 < nck) stage(Rn, (c + 1) & 1);
-    if (c + 1 + kDepth < nck) load(Rn, c + 1 + kDepth);
-    __syncthreads();
-  };
-  // steady state, branch-free: every step stages and refills its register set
-  int c = 0;
-  for (; c + 2 * kDepth < nck; c += kDepth) {
-#pragma unroll
-    for (int j = 0; j < kDepth; ++j) {
-      multiply((c + j) & 1);
-      stage(R[(j + 1) % kDepth], (c + j + 1) & 1);
-      load(R[(j + 1) % kDepth], c + j + 1 + kDepth);
-      __syncthreads();
+    if (c + 1 < nck) {
+      stage_w((c + 1) & 1);
+      load_w(c + 2);
     }
+    __syncthreads();
   }
-  for (; c < nck; c += kDepth) {
-#pragma unroll
-    for (int j = 0; j < kDepth; ++j)
-      if (c + j < nck) step(c + j, R[(j + 1) % kDepth]);
+  if (nmin < nck) {  // the longer half's last chunk
+    if (na == nck) {
+      stage_a();
+      multiply(nmin & 1);
+    }
+    __syncthreads();
   }
-  if (!mma) return;
-  float* out = Zpart + (int64_t)s * part_stride;
+  // the K halves: wave w < 4 keeps row tile 0 and gives row tile 1 to wave w + 4
+  float* ex = reinterpret_cast<float*>(Ws) + wave * (16 * UB);
 #pragma unroll
-  for (int f = 0; f < 2; ++f) {
+  for (int q = 0; q < UB / 64; ++q)
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const int r = 32 * wr + 16 * f + 4 * (lane >> 4) + t;
-      if (r >= rows) continue;
-      float* o = out + ((int64_t)e0 * kBatch + r) * H + u0 + 64 * wu + (lane & 15);
+      const int f = kh ? 0 : 1;
+      f32x4 v;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) o[16 * u] = acc[f][u][t];
+      for (int j = 0; j < 4; ++j) v[j] = f ? acc[1][4 * q + j][t] : acc[0][4 * q + j][t];
+      *reinterpret_cast<f32x4*>(ex + ((q * 4 + t) * 64 + lane) * 4) = v;
+    }
+  __syncthreads();
+  if (!live) return;
+  const float* got = reinterpret_cast<const float*>(Ws) + (wave ^ 4) * (16 * UB);
+  float* out = Zpart + (int64_t)s * part_stride + ((int64_t)(e0 + mb) * kBatch + 16 * kh) * H + u0 + 4 * i;
+#pragma unroll
+  for (int q = 0; q < UB / 64; ++q) {
+    if (64 * q >= units) break;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const f32x4 o = *reinterpret_cast<const f32x4*>(got + ((q * 4 + t) * 64 + lane) * 4);
+      f32x4 v;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = kh ? o[j] + acc[1][4 * q + j][t] : acc[0][4 * q + j][t] + o[j];
+      *reinterpret_cast<f32x4*>(out + (int64_t)(4 * g + t) * H + 64 * q) = v;
     }
   }
 }
@@ -661,6 +696,21 @@ nbsgd_status launch_err(const char* what) {
 
 uint32_t item(int learner, int slot) { return ((uint32_t)learner << 24) | ((uint32_t)slot << 12); }
 
+// Slices of d_in for `tiles` 128 x 128 output tiles: the count that makes rounds of
+// workgroups (one fits a CU, 256 a round) times chunks in a half slice the least,
+// the fewer slices on a tie, since every slice adds a plane of partial sums that is
+// written and read (4,096 samples, 128 tiles, 2 slices: 43.3 us a call; 256-row
+// blocks in 4 slices 45.6; the 8 x 8 workload's 50 tiles take 4).
+int fwd_slices(int d_in, int tiles) {
+  const int T = d_in / kFwKc;
+  int best = 0, least = 0;
+  for (int q = 1; q <= kSkMaxSlices && 2 * q <= T; ++q) {
+    const int cost = (tiles * q + 255) / 256 * ((T + 2 * q - 1) / (2 * q));
+    if (!best || cost < least) best = q, least = cost;
+  }
+  return best;
+}
+
 // Launches the kernels over mini-batches `mb` (learner, slot), sorted by
 // learner, of one group (at most kMaxList): the sample indices host_idx[slot
 // * 32 ..] (checked) go to the workspace in the forward kernel's arguments
@@ -676,28 +726,24 @@ void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_
   // forward over quads of each learner's mini-batches, slices of d_in
   SkMap K;
   memset(&K, 0, sizeof K);
-  const int chunks = d.d_in / kSkKc;
-  K.S = 1;
-  for (int q = kSkMaxSlices; q >= 1; --q)
-    if (chunks % q == 0) {
-      K.S = q;
-      break;
-    }
-  K.ub = (d.hidden + kSkUnits - 1) / kSkUnits;
+  K.ub = (d.hidden + kFwUnits - 1) / kFwUnits;
   int sk_total = 0;
   for (int k = 0; k < items.count; ++k) {
     if (k == 0 || item_learner(items.w[k]) != item_learner(items.w[k - 1])) {
-      if (K.n > 0) sk_total += K.S * K.ub * ((k - K.first[K.n - 1] + 3) / 4);
-      K.off[K.n] = sk_total;
       K.first[K.n] = k;
       K.learner[K.n >> 2] |= (uint32_t)item_learner(items.w[k]) << (8 * (K.n & 3));
       ++K.n;
     }
   }
-  sk_total += K.S * K.ub * ((items.count - K.first[K.n - 1] + 3) / 4);
-  K.off[K.n] = sk_total;
   K.first[K.n] = items.count;
-  // each XCD's range of work items holds at most ceil(total / 8)
+  int tiles = 0;
+  for (int k = 0; k < K.n; ++k) tiles += K.ub * ((K.first[k + 1] - K.first[k] + kFwMb - 1) / kFwMb);
+  K.S = fwd_slices(d.d_in, tiles);
+  for (int k = 0; k < K.n; ++k) {
+    K.off[k] = sk_total;
+    sk_total += K.S * K.ub * ((K.first[k + 1] - K.first[k] + kFwMb - 1) / kFwMb);
+  }
+  K.off[K.n] = sk_total;
   const dim3 fgrid(8 * ((sk_total + 7) / 8));
   if (!wide && count <= kInline) {
     InlineIdx I;
@@ -709,12 +755,12 @@ void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_
         I.v[t >> 1] |= (uint32_t)src[r] << (16 * (t & 1));
       }
     }
-    hipLaunchKernelGGL(k_mlp_fwd_sk<true>, fgrid, dim3(512), 0, st, X, data, w.idx, w.part,
+    hipLaunchKernelGGL(k_mlp_fwd<true>, fgrid, dim3(64 * kFwWaves), 0, st, X, data, w.idx, w.part,
                        w.part_stride, d, K, I);
   } else {
     put_idx(host_idx, mb, count, wide, w, st);
     const Idx16<1> none = {{0u}};
-    hipLaunchKernelGGL(k_mlp_fwd_sk<false>, fgrid, dim3(512), 0, st, X, data, w.idx, w.part,
+    hipLaunchKernelGGL(k_mlp_fwd<false>, fgrid, dim3(64 * kFwWaves), 0, st, X, data, w.idx, w.part,
                        w.part_stride, d, K, none);
   }
   hipLaunchKernelGGL(k_mlp_head<BACKWARD>, dim3(items.count), dim3(kHeadThreads), 0, st, X, w.idx,

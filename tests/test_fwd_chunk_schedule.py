@@ -1,8 +1,8 @@
 """The forward GEMM's chunk pipeline, walked on the CPU for every chunk count
 the d_in splits can give (1 .. 48): two register sets and two LDS buffers,
 chunks loaded kDepth ahead with indices clamped to the last chunk, a
-branch-free steady loop and a guarded tail, as in k_mlp_fwd_sk
-(paper_2211_00889_amd/csrc/mlp.hip).  Checks that every chunk is multiplied
+branch-free steady loop and a guarded tail; and with one register set, as
+k_mlp_fwd (paper_2211_00889_amd/csrc/mlp.hip) stages W1.  Checks that every chunk is multiplied
 exactly once, in order, from the buffer it was staged into, that a register
 set is only refilled after it was staged, and that a buffer is only
 restaged after the barrier that follows its last multiply."""
@@ -73,6 +73,15 @@ def walk(nck, depth=K_DEPTH, mistake=False):
 @pytest.mark.parametrize("nck", range(1, 49))
 def test_every_chunk_multiplied_once_in_order(nck):
     multiplied, staged_from = walk(nck)
+    assert multiplied == list(range(nck))
+    assert all(staged_from[c] == (c & 1) for c in range(nck))
+
+
+@pytest.mark.parametrize("nck", range(1, 25))
+def test_one_register_set(nck):
+    """k_mlp_fwd's order: load 0, stage 0, load 1; then per chunk multiply, stage
+    the next, load the one after it, barrier (1-24 chunks: half a slice of d_in)."""
+    multiplied, staged_from = walk(nck, depth=1)
     assert multiplied == list(range(nck))
     assert all(staged_from[c] == (c & 1) for c in range(nck))
 
