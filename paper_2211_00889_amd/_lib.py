@@ -122,42 +122,63 @@ def _check(status: int):
         raise NbsgdError(status, load().nbsgd_last_error().decode())
 
 
-def _host_ptr(a: np.ndarray):
-    return a.ctypes.data_as(_c_void_p)
+# A small step is bound by the host: its marshalling took 9 of the 12 us between
+# two calls (kernel 4.6 us).  Host arrays that the library only reads go as bytes
+# objects and pointers as plain integers, both of which ctypes passes without
+# building objects (a data_as pointer costs 2.2 us, the bytes of a mask 0.1), and
+# torch is imported once.
+_torch = None
+_raw_stream = None
 
 
-def _dev(t, name):
-    import torch
+def _use_torch():
+    global _torch, _raw_stream
+    if _torch is None:
+        import torch
 
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda index: torch.cuda.current_stream(index).cuda_stream)
+        _torch = torch
+    return _torch
+
+
+def _host_ptr(a: np.ndarray) -> int:
+    """Address of a host array that the library writes (and the caller keeps)."""
+    return a.ctypes.data
+
+
+def _dev(t, name) -> int:
+    torch = _torch or _use_torch()
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA tensor")
     if t.dtype != torch.float32 or not t.is_contiguous():
         raise TypeError(f"{name} must be contiguous float32")
-    return _c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(t, stream):
-    import torch
-
+def _stream(t, stream) -> int:
     if stream is None:
-        return _c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
-    if isinstance(stream, torch.cuda.Stream):
-        return _c_void_p(stream.cuda_stream)
-    return _c_void_p(int(stream))
+        if _raw_stream is None:
+            _use_torch()
+        return _raw_stream(t.get_device())
+    if isinstance(stream, _use_torch().cuda.Stream):
+        return stream.cuda_stream
+    return int(stream)
 
 
-def _u8(a, shape):
+def _u8(a, shape) -> bytes:
+    """The host array as the library's uint8 input of this shape."""
     a = np.ascontiguousarray(np.asarray(a), dtype=np.uint8)
     if a.shape != shape:
         raise ValueError(f"expected shape {shape}, got {a.shape}")
-    return a
+    return a.tobytes()
 
 
-def _w32(W, n):
+def _w32(W, n) -> bytes:
     W = np.ascontiguousarray(np.asarray(W), dtype=np.float32)
     if W.shape != (n, n):
         raise ValueError(f"W must be {n}x{n}")
-    return W
+    return W.tobytes()
 
 
 # ------------------------------------------------------------------ host calls
@@ -256,7 +277,7 @@ def accumulate(G, mask, Gbar, stream=None):
     mask = _u8(mask, (n, m))
     if tuple(Gbar.shape) != (n, P):
         raise ValueError("Gbar must be [n, P]")
-    _check(load().nbsgd_accumulate(_dev(G, "G"), _host_ptr(mask), n, m, P, _dev(Gbar, "Gbar"),
+    _check(load().nbsgd_accumulate(_dev(G, "G"), mask, n, m, P, _dev(Gbar, "Gbar"),
                                    _stream(G, stream)))
 
 
@@ -265,7 +286,7 @@ def mix(X, W, Y, stream=None):
     W = _w32(W, n)
     if tuple(Y.shape) != (n, P):
         raise ValueError("Y must be [n, P]")
-    _check(load().nbsgd_mix(_dev(X, "X"), _host_ptr(W), n, P, _dev(Y, "Y"), _stream(X, stream)))
+    _check(load().nbsgd_mix(_dev(X, "X"), W, n, P, _dev(Y, "Y"), _stream(X, stream)))
 
 
 def update(X, V, Gbar, counts, m: int, lr: float, momentum: float, stream=None):
@@ -273,7 +294,7 @@ def update(X, V, Gbar, counts, m: int, lr: float, momentum: float, stream=None):
     counts = np.ascontiguousarray(np.asarray(counts), dtype=np.int32)
     if counts.shape != (n,) or tuple(V.shape) != (n, P) or tuple(Gbar.shape) != (n, P):
         raise ValueError("shape mismatch")
-    _check(load().nbsgd_update(_dev(X, "X"), _dev(V, "V"), _dev(Gbar, "Gbar"), _host_ptr(counts),
+    _check(load().nbsgd_update(_dev(X, "X"), _dev(V, "V"), _dev(Gbar, "Gbar"), counts.tobytes(),
                                n, m, P, lr, momentum, _stream(X, stream)))
 
 
@@ -283,8 +304,8 @@ def step(X, V, G, mask, W, lr: float, momentum: float, order: int, stream=None):
         raise ValueError("X and V must be [n, P] with G [n, m, P]")
     mask = _u8(mask, (n, m))
     W = _w32(W, n)
-    _check(load().nbsgd_step(_dev(X, "X"), _dev(V, "V"), _dev(G, "G"), _host_ptr(mask),
-                             _host_ptr(W), n, m, P, lr, momentum, order, _stream(X, stream)))
+    _check(load().nbsgd_step(_dev(X, "X"), _dev(V, "V"), _dev(G, "G"), mask,
+                             W, n, m, P, lr, momentum, order, _stream(X, stream)))
 
 
 def step_strided(X, V, G, P: int, mask, W, lr: float, momentum: float, order: int, stream=None):
@@ -295,8 +316,8 @@ def step_strided(X, V, G, P: int, mask, W, lr: float, momentum: float, order: in
         raise ValueError("X and V must be [n, ld] with G [n, m, ld]")
     mask = _u8(mask, (n, m))
     W = _w32(W, n)
-    _check(load().nbsgd_step_strided(_dev(X, "X"), _dev(V, "V"), _dev(G, "G"), ld, _host_ptr(mask),
-                                     _host_ptr(W), n, m, P, lr, momentum, order, _stream(X, stream)))
+    _check(load().nbsgd_step_strided(_dev(X, "X"), _dev(V, "V"), _dev(G, "G"), ld, mask,
+                                     W, n, m, P, lr, momentum, order, _stream(X, stream)))
 
 
 def step_server(x, V, G, P: int, mask, lr: float, momentum: float, stream=None):
@@ -306,7 +327,7 @@ def step_server(x, V, G, P: int, mask, lr: float, momentum: float, stream=None):
     if tuple(V.shape) != (n, ld) or x.dim() != 1 or x.shape[0] < P:
         raise ValueError("V must be [n, ld] and x hold P floats, with G [n, m, ld]")
     mask = _u8(mask, (n, m))
-    _check(load().nbsgd_step_server(_dev(x, "x"), _dev(V, "V"), _dev(G, "G"), ld, _host_ptr(mask), n, m,
+    _check(load().nbsgd_step_server(_dev(x, "x"), _dev(V, "V"), _dev(G, "G"), ld, mask, n, m,
                                     P, lr, momentum, _stream(x, stream)))
 
 
@@ -341,20 +362,18 @@ def minibatch_indices(seed: int, step: int, n: int, m: int, b: int, shard: int) 
     return idx
 
 
-def _i32_dev(t, name):
-    import torch
-
+def _i32_dev(t, name) -> int:
+    torch = _torch or _use_torch()
     if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != torch.int32 or not t.is_contiguous():
         raise TypeError(f"{name} must be a contiguous int32 CUDA tensor")
-    return _c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _ws(t):
-    import torch
-
+    torch = _torch or _use_torch()
     if not isinstance(t, torch.Tensor) or not t.is_cuda or not t.is_contiguous():
         raise TypeError("workspace must be a contiguous CUDA tensor")
-    return _c_void_p(t.data_ptr()), t.numel() * t.element_size()
+    return t.data_ptr(), t.numel() * t.element_size()
 
 
 def _mlp_grad_args(X, m, dims, data, labels, idx, mask, G, losses, ld):
@@ -378,8 +397,8 @@ def mlp_grad(X, m: int, dims, data, labels, idx, mask, G, losses, workspace, str
                                   mlp_param_count(*dims))
     ws, ws_bytes = _ws(workspace)
     _check(load().nbsgd_mlp_grad(_dev(X, "X"), n, m, ctypes.byref(_shape(*dims)), _dev(data, "data"),
-                                 _i32_dev(labels, "labels"), data.shape[0], _host_ptr(idx),
-                                 _host_ptr(mask), _dev(G, "G"), _dev(losses, "losses"), ws, ws_bytes,
+                                 _i32_dev(labels, "labels"), data.shape[0], idx.tobytes(),
+                                 mask, _dev(G, "G"), _dev(losses, "losses"), ws, ws_bytes,
                                  _stream(X, stream)))
 
 
@@ -391,7 +410,7 @@ def mlp_grad_strided(X, m: int, dims, data, labels, idx, mask, G, losses, worksp
     ws, ws_bytes = _ws(workspace)
     _check(load().nbsgd_mlp_grad_strided(_dev(X, "X"), ld, n, m, ctypes.byref(_shape(*dims)),
                                          _dev(data, "data"), _i32_dev(labels, "labels"),
-                                         data.shape[0], _host_ptr(idx), _host_ptr(mask), _dev(G, "G"),
+                                         data.shape[0], idx.tobytes(), mask, _dev(G, "G"),
                                          _dev(losses, "losses"), ws, ws_bytes, _stream(X, stream)))
 
 
@@ -402,7 +421,7 @@ def mlp_grad_noalloc(X, m: int, dims, data, labels, idx, mask, G, losses, stream
     n, idx, mask = _mlp_grad_args(X, m, dims, data, labels, idx, mask, G, losses, ld)
     _check(load().nbsgd_mlp_grad_noalloc(_dev(X, "X"), ld, n, m, ctypes.byref(_shape(*dims)),
                                          _dev(data, "data"), _i32_dev(labels, "labels"),
-                                         data.shape[0], _host_ptr(idx), _host_ptr(mask), _dev(G, "G"),
+                                         data.shape[0], idx.tobytes(), mask, _dev(G, "G"),
                                          _dev(losses, "losses"), _stream(X, stream)))
 
 
@@ -414,5 +433,5 @@ def mlp_loss(params, dims, data, labels, idx, losses, workspace, stream=None):
     idx = np.ascontiguousarray(np.asarray(idx), dtype=np.int32).reshape(-1)
     ws, ws_bytes = _ws(workspace)
     _check(load().nbsgd_mlp_loss(_dev(params, "params"), ctypes.byref(_shape(*dims)), _dev(data, "data"),
-                                 _i32_dev(labels, "labels"), data.shape[0], _host_ptr(idx), idx.size,
+                                 _i32_dev(labels, "labels"), data.shape[0], idx.tobytes(), idx.size,
                                  _dev(losses, "losses"), ws, ws_bytes, _stream(params, stream)))
