@@ -34,7 +34,10 @@ def test_tiles_cover_every_column_once(tmp_path):
 # single floats.
 EDGES = [(1, 1), (255, 255), (256, 257), (257, 288), (1023, 1023), (1024, 1028), (1025, 1025),
          (1027, 1056), (8191, 8191), (8192, 8193), (8193, 8224), (8449, 8449), (8446, 8446),
-         (16640, 16644), (33284, 33284)]
+         (16640, 16644), (33284, 33284),
+         # up to 35 rows of these are above and below the 128 MiB that the step reads
+         # through the caches (the counts decide)
+         (1_000_003, 1_000_003), (1_200_004, 1_200_128)]
 
 
 @pytest.mark.gpu
