@@ -7,12 +7,11 @@
 // conversion) and multiplied with fp32 accumulation:
 //   k_mlp_fwd    partial Z1 = A W1 over one slice of d_in, per 128-row x
 //                128-unit tile, on MFMA 16x16x32 (both operands staged in LDS)
-//   k_mlp_head   per mini-batch: Z1 = sum of the slices + b1, H =
-//                 bf16(relu(Z1)), logits = H W2 + b2 (MFMA, classes padded to
-//                 16), softmax-CE, dZ2; dZ1 = (dZ2 W2^T) * [Z1 > 0], db1, dW2 =
-//                 H^T dZ2 (MFMA), db2 and the loss
-//   k_mlp_wgrad  dW1 = A^T dZ1 on MFMA 16x16x32 (K = batch = 32), staged per
-//                16-feature tile through LDS and stored as whole row pieces
+//   k_mlp_back   per mini-batch: Z1 = sum of the slices + b1, H =
+//                bf16(relu(Z1)), logits = H W2 + b2 (MFMA, classes padded to
+//                16), softmax-CE, the loss; and for gradients dZ2, dZ1 = (dZ2
+//                W2^T) * [Z1 > 0], db1, dW2 = H^T dZ2, db2 and dW1 = A^T dZ1
+//                (MFMA, K = batch = 32)
 // MFMA 16x16x32 bf16 operand layout (lane l, t = 0..7): A[l % 16][8 (l / 16) + t],
 // B[8 (l / 16) + t][l % 16]; result D[4 (l / 16) + t][l % 16], t = 0..3.
 //
@@ -45,7 +44,6 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 // kBatch, kMaxHidden, kMaxClasses, kFeatBlock, kSkMaxSlices and Dims: mlp_shape.h
 constexpr int kMaxList = 896;    // mini-batches per launch group (kernel-argument list)
 constexpr int kMaxEval = 512;    // batches of 32 per nbsgd_mlp_loss call
-constexpr int kHeadThreads = 1024;  // 16 waves per mini-batch in k_mlp_head
 
 // One launch group's mini-batches, word e = learner << 24 | slot << 12,
 // sorted by learner.  A slot indexes the caller's sample list (slot * 32 ..),
@@ -82,8 +80,6 @@ static_assert(kMaxList <= 4096 && kMaxEval <= 4096, "slots are packed in 16 bits
 
 __host__ __device__ __forceinline__ int item_learner(uint32_t w) { return (int)(w >> 24); }
 __device__ __forceinline__ int item_slot(uint32_t w) { return (int)((w >> 12) & 0xfffu); }
-
-__device__ __forceinline__ float bf16r(float x) { return (float)(__bf16)x; }
 
 // Two (eight) floats to bf16 as one vector conversion: one v_cvt_pk_bf16_f32 a
 // pair.  Converted one by one and combined by hand they took seven instructions a
@@ -124,7 +120,7 @@ __global__ void __launch_bounds__(256) k_put_idx(int32_t* __restrict__ dst, IdxC
 // free of bank conflicts; a 64-unit group's unit 4 q + t is LDS row 16 t + q, so
 // that lane q of a result holds four consecutive units.  The two halves are added
 // through LDS at the end (first half + second half) and the sum goes to slice s
-// of the partial buffer; k_mlp_head adds the slices in slice order.
+// of the partial buffer; k_mlp_back adds the slices in slice order.
 // What bounds it: with samples and W1 cold (8 x 8 workload, 73 MB) their fetch, 27-33
 // us; with 4,096 samples of one learner the chunk's chain of staging, LDS reads and
 // MFMAs and the partial sums' write, 26 us (45.8 with 32-row x 64-unit waves,
@@ -335,127 +331,182 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
   }
 }
 
-// Per list entry e = blockIdx.x (workspace rows e * 32 ..; G row and loss of
-// its slot), all hidden units, 16 waves: the rows' labels (clamped into
-// [0, classes)); Z1 = the S
-// partial slices summed in slice order + b1 (kept in LDS); the logits =
-// bf16(relu(Z1)) bf16(W2) + b2 on the matrix cores (classes zero-padded to
-// 16; each wave takes every sixteenth 32-unit K step and the waves' partial
-// sums are added in wave order); softmax cross-entropy, the loss and dZ2 =
-// (softmax - onehot) / 32.  When BACKWARD, wave w takes the unit tiles
-// 16 (w + 16 k) .. +15 on the matrix cores: dZ1 = (bf16(dZ2) bf16(W2)^T) *
-// [Z1 > 0] (K = classes, zero-padded to 32), stored in bf16 as
-// [entry][unit][row] for k_mlp_wgrad, db1 = its sum over the rows, and dW2 =
-// bf16(relu(Z1))^T bf16(dZ2) (K = the 32 rows); then db2 and the padding of G.
+// Per list entry e = blockIdx.x (workspace rows e * 32 ..; G row and loss of its
+// slot) and, when BACKWARD, every gridDim.y-th block of 128 features from
+// blockIdx.y.  Eight waves, 32 rows, all hidden units:
+//   Z1 = the S partial slices summed in slice order + b1; kept in LDS as bf16
+//   relu(Z1), with -0 where Z1 is not above zero, which is the ReLU's mask
+//   logits = relu(Z1) bf16(W2) + b2 on the matrix cores (classes zero-padded to
+//   16; wave w takes the 32-unit K steps w and w + 8, the waves' sums are added in
+//   wave order), softmax cross-entropy by one thread per (row, class), the loss
+//   and dZ2 = (softmax - onehot) / 32
+//   dZ1 = (bf16(dZ2) bf16(W2)^T) * [Z1 > 0], which stays in registers: a result's
+//   rows 4 g + t and 16 + 4 g + t (g = lane / 16) are the K order of the dW1 product,
+//   kk(g, t), so the two row tiles of a unit are its B fragment as they are
+//   (unit 4 i + j of a 64-unit group in lane i of tile j)
+//   dW1[f][h] = sum_r bf16(A[s_r][f]) bf16(dZ1[r][h]): A fragments (16 features, the
+//   rows in kk order) from the sample columns staged in LDS, two buffers; a wave
+//   takes two groups of units, swaps half rows between their results
+//   (v_permlane16_swap) and stores 512 contiguous bytes of two G rows at a time
+//   workgroups blockIdx.y == 0 write db1 (row sums by lane shuffles), dW2 =
+//   relu(Z1)^T dZ2 (the mask's registers are its A fragment), db2, the padding of
+//   G and the loss
+// Bound by the 299 MB of G that the 8 x 8 workload writes (48 us at the 6.2 TB/s of
+// a large copy; 58-60 us here) after 10 us to the first store.  It replaces a head
+// kernel, one 1024-thread workgroup per mini-batch (15.8 us, 209 CUs idle), that
+// passed dZ1 through memory to a dW1 kernel (53.2 us): recomputing the head in
+// every workgroup costs less than its launch on few CUs.  The features are taken
+// in turns, so that all workgroups write G in increasing column order and the
+// step, which reads from the last column, finds the newest in the memory-side
+// cache (a contiguous range per workgroup: 97.1 against 95.9 us, and a slower step).
+constexpr int kBackThreads = 512, kBackWaves = kBackThreads / 64;
+// workgroups that take one entry's features: as many as keep the launch within one
+// workgroup per CU, since the head costs each of them 10 us, but at most six blocks
+// each (8 x 4 mini-batches 3072x512: 62.6 us so, 64.1 with two per CU; 12 x 8 of
+// 1408x512 79.9 and 82.5; 16 x 16 373.4 and 371.2 with at most four)
+constexpr int kBackGrid = 256, kBackBlocks = 6;
+
 template <bool BACKWARD>
-__global__ void __launch_bounds__(kHeadThreads)
-    k_mlp_head(const float* __restrict__ X, const int32_t* __restrict__ idx,
-               const int32_t* __restrict__ labels, const float* __restrict__ Zpart,
-               int64_t part_stride, int S,
-               __bf16* __restrict__ dZ1t, float* __restrict__ G, float* __restrict__ losses, Dims d,
-               List L) {
-  constexpr int kLdz = kMaxHidden + 4;
-  __shared__ __attribute__((aligned(16))) float Z1s[kBatch * kLdz];  // Z1 [row][unit]
-  __shared__ float W2s[kMaxHidden * kMaxClasses];                     // bf16(W2), [unit][class]
-  __shared__ float Zs[kBatch * kMaxClasses];  // logits, then dZ2
-  __shared__ float Zb[kBatch * kMaxClasses];  // bf16(dZ2), zero beyond the classes
+__global__ void __launch_bounds__(kBackThreads, 4)
+    k_mlp_back(const float* __restrict__ X, const float* __restrict__ data,
+               const int32_t* __restrict__ idx, const int32_t* __restrict__ labels,
+               const float* __restrict__ Zpart, int64_t part_stride, int S, float* __restrict__ G,
+               float* __restrict__ losses, Dims d, List L) {
+  constexpr int kLdh = kMaxHidden + 8;  // bf16 per row of Hs
+  __shared__ __attribute__((aligned(16))) __bf16 Hs[kBatch * kLdh];
+  __shared__ __attribute__((aligned(16))) __bf16 W2s[kMaxHidden * kMaxClasses];  // [unit][16]
+  __shared__ float Zs[kBatch * kMaxClasses];                     // dZ2
+  __shared__ __attribute__((aligned(16))) __bf16 Zb[kBatch * kMaxClasses];  // bf16(dZ2)
   __shared__ float row_loss[kBatch];
   __shared__ int ys[kBatch];
-  __shared__ float Lp[(kHeadThreads / 64) * kBatch * 16];  // each wave's partial logits
-  const uint32_t item = L.w[blockIdx.x];
+  // each wave's partial logits, then the sample columns of two feature blocks
+  __shared__ __attribute__((aligned(16))) float Lp[kBackWaves * kBatch * 16];
+  static_assert(sizeof(Lp) == 2 * kFeatBlock * kBatch * sizeof(__bf16), "two buffers");
+  __bf16* At = reinterpret_cast<__bf16*>(Lp);
+  const int e = blockIdx.x;
+  if (e >= L.count) return;  // uniform
+  const uint32_t item = L.w[e];
   const int slot = item_slot(item);
   const float* prm = X + (int64_t)item_learner(item) * d.ld;
   const int H = d.hidden, C = d.classes;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t row0 = (int64_t)blockIdx.x * kBatch;
-  const int32_t sample = tid < kBatch ? idx[row0 + tid] : 0;  // loaded ahead of its use
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, g = lane >> 4;
+  const int64_t row0 = (int64_t)e * kBatch;
+  const int nb = d.d_in / kFeatBlock;
+  const int blk0 = blockIdx.y, step = gridDim.y;  // blocks blk0, blk0 + step, ..
+  const bool first = BACKWARD && blockIdx.y == 0;  // writes what is not dW1
 
-  // Z1: thread takes row tid / TPR and units uq + SPAN j, uq = 4 (tid % TPR).
-  // Every load of this phase (the slices, b1, W2 and the label) is issued
-  // before any of them is used, so the phase costs one memory round trip.
-  constexpr int TPR = kHeadThreads / 32, SPAN = 4 * TPR;
-  constexpr int kW2Loads = kMaxHidden * kMaxClasses / kHeadThreads;
-  static_assert(4 * SPAN >= kMaxHidden && kW2Loads * kHeadThreads == kMaxHidden * kMaxClasses,
-                "one pass of the phase covers every unit and every W2 entry");
-  float b2v;  // b2 of class tid % 16, for the softmax thread (row tid / 16, class tid % 16)
+  const int32_t sample = idx[row0 + (tid & (kBatch - 1))];
+  // samples: rows 2 pr, 2 pr + 1, features fq .. +3 of a block
+  const int pr = tid >> 5, fq = 4 * (tid & 31);
+  const float* s0 = data + (int64_t)idx[row0 + 2 * pr] * d.d_in + fq;
+  const float* s1 = data + (int64_t)idx[row0 + 2 * pr + 1] * d.d_in + fq;
+  f32x4 x0, x1;
+
+  float b2v;
   {
-    const int r = tid / TPR, uq = 4 * (tid % TPR);
+    // Z1: row r, units uq + 64 j; every load of a half is issued before any is
+    // used, and the rest of the phase's with the first half's
+    const int r = tid >> 4, uq = 4 * (tid & 15);
     const float* src = Zpart + (row0 + r) * H + uq;
-    f32x4 p[kSkMaxSlices][4], b[4];
+    const float* pb = prm + d.off_b1 + uq;
+    const float* pw = prm + d.off_w2 + (int64_t)min(tid, H - 1) * C;
+    float w2[kMaxClasses];
+    int32_t y;
 #pragma unroll
-    for (int q = 0; q < kSkMaxSlices; ++q)
+    for (int h = 0; h < 2; ++h) {
+      if (256 * h >= H) break;
+      f32x4 p[kSkMaxSlices][4], b[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        p[q][j] = (q < S && uq + SPAN * j < H)
-                      ? *reinterpret_cast<const f32x4*>(src + (int64_t)q * part_stride + SPAN * j)
-                      : f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < 4; ++j) {
+        const int u = 64 * (4 * h + j);
+        if (u < H) {  // uniform, as every condition on j and q here
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      b[j] = uq + SPAN * j < H ? *reinterpret_cast<const f32x4*>(prm + d.off_b1 + uq + SPAN * j)
-                               : f32x4{0.f, 0.f, 0.f, 0.f};
-    float w2[kW2Loads];
+          for (int q = 0; q < kSkMaxSlices; ++q)
+            if (q < S) p[q][j] = *reinterpret_cast<const f32x4*>(src + (int64_t)q * part_stride + u);
+          b[j] = *reinterpret_cast<const f32x4*>(pb + u);
+        }
+      }
+      if (h == 0) {
+        y = labels[sample];
+        b2v = prm[d.off_b2 + min(tid & 15, C - 1)];
+        if (BACKWARD) {
+          x0 = *reinterpret_cast<const f32x4*>(s0 + blk0 * kFeatBlock);
+          x1 = *reinterpret_cast<const f32x4*>(s1 + blk0 * kFeatBlock);
+        }
+      }
 #pragma unroll
-    for (int k = 0; k < kW2Loads; ++k) {
-      const int e = tid + k * kHeadThreads;
-      w2[k] = e < H * C ? prm[d.off_w2 + e] : 0.0f;
+      for (int j = 0; j < 4; ++j) {
+        const int u = 64 * (4 * h + j);
+        if (u < H) {
+          f32x4 z = p[0][j];
+#pragma unroll
+          for (int q = 1; q < kSkMaxSlices; ++q)
+            if (q < S) z += p[q][j];
+          z += b[j];
+          // relu(z) in bf16; -0 where z is not above zero
+#pragma unroll
+          for (int t = 0; t < 4; ++t) z[t] = z[t] > 0.0f ? z[t] : -0.0f;
+          const uint2 v = {pack_bf16(z[0], z[1]), pack_bf16(z[2], z[3])};
+          *reinterpret_cast<uint2*>(Hs + r * kLdh + uq + u) = v;
+        }
+      }
+      if (h == 0) {
+#pragma unroll
+        for (int k = 0; k < kMaxClasses; ++k)
+          if (k < C) w2[k] = pw[k];
+      }
     }
-    const int32_t y = tid < kBatch ? labels[sample] : 0;
-    b2v = tid < kBatch * 16 && (tid & 15) < C ? prm[d.off_b2 + (tid & 15)] : 0.0f;
+    uint32_t wv[kMaxClasses / 2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (uq + SPAN * j >= H) break;
-      f32x4 z = p[0][j];
-#pragma unroll
-      for (int q = 1; q < kSkMaxSlices; ++q)
-        if (q < S) z += p[q][j];
-      z += b[j];
-      *reinterpret_cast<f32x4*>(Z1s + r * kLdz + uq + SPAN * j) = z;
-    }
-#pragma unroll
-    for (int k = 0; k < kW2Loads; ++k) {
-      const int e = tid + k * kHeadThreads;
-      if (e < H * C) W2s[e] = bf16r(w2[k]);
+    for (int k = 0; k < kMaxClasses / 2; ++k)
+      wv[k] = pack_bf16(2 * k < C ? w2[2 * k] : 0.0f, 2 * k + 1 < C ? w2[2 * k + 1] : 0.0f);
+    if (tid < H) {
+      *reinterpret_cast<uint4*>(W2s + tid * kMaxClasses) = (uint4){wv[0], wv[1], wv[2], wv[3]};
+      *reinterpret_cast<uint4*>(W2s + tid * kMaxClasses + 8) = (uint4){wv[4], wv[5], wv[6], wv[7]};
     }
     if (tid < kBatch) ys[tid] = y < 0 ? 0 : (y >= C ? C - 1 : y);
   }
+  // position of row 2 pr of a sample column: rows 4 g + t and 16 + 4 g + t at 8 g + t and 8 g + 4 + t
+  const int rr = 2 * pr, opos = (rr & 15) >> 2, wpos = (rr & 3) + 4 * (rr >> 4);
+  // octet of a sample column's 32 rows: in the 16 columns of a fragment read, equal
+  // bank groups (columns four apart) get four values, {0, 1} and {2, 3} for the two
+  // halves of the hardware's 16-lane passes
+  auto aswz = [](int f) { const int q = (f >> 2) & 3; return (((q ^ (q >> 1)) & 1) << 1) | (q >> 1); };
+  auto stage_x = [&](int buf) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int f = fq + c;
+      *reinterpret_cast<uint32_t*>(&At[buf * kFeatBlock * kBatch + f * kBatch + 8 * (opos ^ aswz(f)) + wpos]) = pack_bf16(x0[c], x1[c]);
+    }
+  };
   __syncthreads();
-  // logits = bf16(relu(Z1)) bf16(W2) on the matrix cores: wave w takes the
-  // 32-unit K steps w, w + 16, .. for both 16-row tiles; the waves' partial
-  // sums are added in wave order
   {
-    const int kq8 = 8 * (lane >> 4), cl = lane & 15;
     f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    for (int ks = wave; ks < H / 32; ks += kHeadThreads / 64) {
-      const int u0 = 32 * ks + kq8;
+    for (int ks = wave; ks < H / 32; ks += kBackWaves) {
+      const int u0 = 32 * ks + 8 * g;
       bf16x8 fb;
 #pragma unroll
-      for (int t = 0; t < 8; ++t) fb[t] = (__bf16)(cl < C ? W2s[(u0 + t) * C + cl] : 0.0f);
+      for (int t = 0; t < 8; ++t) fb[t] = W2s[(u0 + t) * kMaxClasses + i];
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt) {
-        const float* z = Z1s + (16 * rt + cl) * kLdz + u0;
-        bf16x8 fa;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) fa[t] = (__bf16)fmaxf(z[t], 0.0f);
+        const bf16x8 fa = *reinterpret_cast<const bf16x8*>(Hs + (16 * rt + i) * kLdh + u0);
         acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb, acc[rt], 0, 0, 0);
       }
     }
-    // lane holds rows 16 rt + 4 (lane / 16) + t of class cl
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
-        Lp[(wave * kBatch + 16 * rt + 4 * (lane >> 4) + t) * 16 + cl] = acc[rt][t];
+      for (int t = 0; t < 4; ++t) Lp[(wave * kBatch + 16 * rt + 4 * g + t) * 16 + i] = acc[rt][t];
   }
   __syncthreads();
-  // softmax cross-entropy, thread (row tid / 16, class tid % 16): the logit
-  // (the waves' partial sums in wave order, + b2), then the row's max and sum
-  // of exponentials over the 16 lanes of the row by xor butterflies (every
-  // lane of a row ends with the same sums)
-  if (tid < kBatch * 16) {
+  {
     const int r = tid >> 4, c = tid & 15;
     const bool live = c < C;
     float z = 0.0f;
-    for (int w = 0; w < kHeadThreads / 64; ++w) z += Lp[(w * kBatch + r) * 16 + c];
+#pragma unroll
+    for (int w = 0; w < kBackWaves; ++w) z += Lp[(w * kBatch + r) * 16 + c];
     z += b2v;
     float zmax = live ? z : -INFINITY;
 #pragma unroll
@@ -467,167 +518,140 @@ __global__ void __launch_bounds__(kHeadThreads)
     const int yr = ys[r];
     if (c == yr) row_loss[r] = lse - z;
     if (BACKWARD) {
-      const float g = live ? (expf(z - lse) - (c == yr ? 1.0f : 0.0f)) * (1.0f / kBatch) : 0.0f;
-      Zs[r * kMaxClasses + c] = g;
-      Zb[r * kMaxClasses + c] = bf16r(g);
+      const float gz = live ? (expf(z - lse) - (c == yr ? 1.0f : 0.0f)) * (1.0f / kBatch) : 0.0f;
+      Zs[r * kMaxClasses + c] = gz;
+      Zb[r * kMaxClasses + c] = (__bf16)gz;
     }
   }
   __syncthreads();
-  float* g = G + (int64_t)slot * d.ld;
-  if (tid == 0) {
+  if ((!BACKWARD || first) && tid == 0) {
     float s = 0.0f;
     for (int r = 0; r < kBatch; ++r) s += row_loss[r];
     losses[slot] = s * (1.0f / kBatch);
   }
   if (!BACKWARD) return;
-  if (tid < C) {
-    float s = 0.0f;
-    for (int r = 0; r < kBatch; ++r) s += Zs[r * kMaxClasses + tid];
-    g[d.off_b2 + tid] = s;
+  stage_x(0);
+  float* gr = G + (int64_t)slot * d.ld;
+  if (first) {
+    if (tid < C) {
+      float s = 0.0f;
+      for (int r = 0; r < kBatch; ++r) s += Zs[r * kMaxClasses + tid];
+      gr[d.off_b2 + tid] = s;
+    }
+    if (tid < d.P - d.off_pad) gr[d.off_pad + tid] = 0.0f;
   }
-  if (tid < d.P - d.off_pad) g[d.off_pad + tid] = 0.0f;
-  const int kq = 8 * (lane >> 4);  // this lane's K offset in a fragment
-  bf16x8 fz[2];                    // A[r][k] = bf16(dZ2[r][k]), row tiles 0 and 1
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-    for (int t = 0; t < 8; ++t)
-      fz[rt][t] = (__bf16)(kq + t < kMaxClasses ? Zb[(16 * rt + (lane & 15)) * kMaxClasses + kq + t] : 0.0f);
-  for (int ut = wave; ut < H / 16; ut += kHeadThreads / 64) {
-    const int hl = 16 * ut + (lane & 15);  // this lane's unit
-    // dZ1 for rows 16 rt .. +15 and units 16 ut .. +15
-    bf16x8 fw;  // B[k][h] = bf16(W2[h][k]), k = class
-#pragma unroll
-    for (int t = 0; t < 8; ++t) fw[t] = (__bf16)(kq + t < C ? W2s[hl * C + kq + t] : 0.0f);
-    float db1 = 0.0f;
+  // the wave's units: two neighbouring groups of 64 (the last may be alone), and
+  // its share of the feature tiles
+  const int ng = H / 64, np = (ng + 1) / 2, parts = kBackWaves / np;
+  const int pair = wave % np, part = wave / np;
+  const bool busy = part < parts, two = 2 * pair + 1 < ng;  // uniform
+  bf16x8 dz[2][4];
+  if (busy) {
+    bf16x8 fz[2];
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fz[rt], fw, acc, 0, 0, 0);
-      // lane holds rows 16 rt + 4 (lane / 16) + t of unit hl
-      const int r0 = 16 * rt + 4 * (lane >> 4);
-      float v[4];
+      fz[rt] = *reinterpret_cast<const bf16x8*>(Zb + (16 * rt + i) * kMaxClasses + 8 * (g & 1));
+      if (g > 1) fz[rt] = (bf16x8)((__bf16)0.0f);
+    }
+    bf16x8 fd;  // B[row kk][class]
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        v[t] = Z1s[(r0 + t) * kLdz + hl] > 0.0f ? acc[t] : 0.0f;
-        db1 += v[t];
+    for (int t = 0; t < 8; ++t) fd[t] = Zb[(4 * g + (t & 3) + 16 * (t >> 2)) * kMaxClasses + i];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int ub = 64 * (2 * pair + (two ? q : 0)) + 4 * i;  // units ub + j, j = tile
+      uint2 h[8];  // H of rows kk(g, t), units ub .. ub + 3
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+        h[t] = *reinterpret_cast<const uint2*>(Hs + (4 * g + (t & 3) + 16 * (t >> 2)) * kLdh + ub);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        // B[class][unit]; classes 16-31 multiply the zeros of fz
+        const bf16x8 fw = *reinterpret_cast<const bf16x8*>(W2s + (ub + j) * kMaxClasses + 8 * (g & 1));
+        f32x4 v[2];
+        float db1 = 0.0f;
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+          v[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fz[rt], fw, (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const uint2 hh = h[4 * rt + t];
+            const uint32_t bits = j < 2 ? hh.x : hh.y;
+            v[rt][t] = (bits >> (j & 1 ? 31 : 15)) & 1 ? 0.0f : v[rt][t];
+            db1 += v[rt][t];
+          }
+        }
+        dz[q][j] = to_bf16(v[0], v[1]);
+        if (first && part == 0 && (q == 0 || two)) {
+          db1 += __shfl_xor(db1, 16);
+          db1 += __shfl_xor(db1, 32);
+          if (lane < 16) gr[d.off_b1 + ub + j] = db1;
+          uint32_t hw[4];
+#pragma unroll
+          for (int o = 0; o < 4; ++o) {
+            const uint32_t a = j < 2 ? h[2 * o].x : h[2 * o].y, b = j < 2 ? h[2 * o + 1].x : h[2 * o + 1].y;
+            hw[o] = j & 1 ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
+          }
+          const bf16x8 fh = __builtin_bit_cast(bf16x8, (uint4){hw[0], hw[1], hw[2], hw[3]});
+          const f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, fd, (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+          if (i < C) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)  // unit of M index 4 g + t
+              gr[d.off_w2 + (int64_t)(64 * (2 * pair + q) + 4 * (4 * g + t) + j) * C + i] = acc[t];
+          }
+        }
       }
-      const uint2 packed = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-      *reinterpret_cast<uint2*>(dZ1t + ((int64_t)blockIdx.x * H + hl) * kBatch + r0) = packed;
-    }
-    // db1: the four row groups of a unit sit in lanes l, l+16, l+32, l+48
-    db1 += __shfl_xor(db1, 16);
-    db1 += __shfl_xor(db1, 32);
-    if (lane < 16) g[d.off_b1 + hl] = db1;
-    // dW2[h][c] for units 16 ut .. +15: A[h][r] = bf16(relu(Z1[r][h])), B[r][c] = bf16(dZ2[r][c])
-    bf16x8 fh, fd;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      fh[t] = (__bf16)fmaxf(Z1s[(kq + t) * kLdz + hl], 0.0f);
-      fd[t] = (__bf16)Zb[(kq + t) * kMaxClasses + (lane & 15)];
-    }
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh, fd, acc, 0, 0, 0);
-    const int c = lane & 15;
-    if (c < C) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int h = 16 * ut + 4 * (lane >> 4) + t;
-        g[d.off_w2 + (int64_t)h * C + c] = acc[t];
-      }
-    }
-  }
-}
-
-// dW1[f][h] = sum_r bf16(A[s_r][f]) bf16(dZ1[r][h]) for one list entry
-// (blockIdx.x) and 128 features f0 .. f0+127 (blockIdx.y), every unit h.
-// Computed transposed, D[h][f] = dZ1^T A: the A operand (8 rows r of one
-// unit) is a 16-byte read of the [entry][unit][row] dZ1 copy, the B operand (8
-// rows of one feature) comes from the sample rows staged transposed in LDS,
-// and each lane's four results are consecutive units of one G row.  Wave w
-// takes the hidden/64 consecutive unit tiles from w * hidden/64; per feature
-// tile it passes its results through its own LDS rows and stores each
-// feature's hidden/4 units as one contiguous piece; a workgroup writes 128
-// whole G rows of dW1.
-__global__ void __launch_bounds__(256)
-    k_mlp_wgrad(const float* __restrict__ data, const int32_t* __restrict__ idx,
-                const __bf16* __restrict__ dZ1t, float* __restrict__ G, Dims d, List L) {
-  constexpr int kLda = kBatch + 8;  // bf16 per transposed sample column (16-byte aligned)
-  __shared__ __attribute__((aligned(16))) __bf16 At[kFeatBlock * kLda];
-  const int slot = item_slot(L.w[blockIdx.x]);
-  const int f0 = blockIdx.y * kFeatBlock;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int H = d.hidden;
-  const int64_t row0 = (int64_t)blockIdx.x * kBatch;
-  // this wave's dZ1 fragments (hidden/64 <= 8 consecutive unit tiles),
-  // loaded before the sample rows so both latencies overlap
-  const __bf16* dz = dZ1t + row0 * H + 8 * (lane >> 4);  // [unit][row] of this mini-batch
-  bf16x8 fa[kMaxHidden / 64];
-  const int per = H / 64;  // unit tiles of this wave: wave * per .. + per - 1
-#pragma unroll
-  for (int u = 0; u < kMaxHidden / 64; ++u) {
-    const int ht = wave * per + u;
-    if (u < per) fa[u] = *reinterpret_cast<const bf16x8*>(dz + (int64_t)(16 * ht + (lane & 15)) * kBatch);
-  }
-  {
-    // rows 2p, 2p+1 (p = tid / 16) of the mini-batch, features 4q .. 4q+3 and
-    // 64 + 4q .. (q = tid % 16): packed pairs of rows into At[f][r].  A row
-    // of At is four 16-byte pieces of 8 samples; piece c of feature f sits at
-    // position c ^ ((f / 16) % 4), so that these writes (features four apart)
-    // and the fragment reads both spread over all LDS banks.
-    const int p = tid >> 4, q = 4 * (tid & 15);
-    const int pw = 4 * ((p >> 2) ^ ((q >> 4) & 3)) + (p & 3);  // dword of row pair p
-    const float* s0 = data + (int64_t)idx[row0 + 2 * p] * d.d_in + f0 + q;
-    const float* s1 = data + (int64_t)idx[row0 + 2 * p + 1] * d.d_in + f0 + q;
-    uint32_t* a32 = reinterpret_cast<uint32_t*>(At);
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const f32x4 x0 = *reinterpret_cast<const f32x4*>(s0 + 64 * h);
-      const f32x4 x1 = *reinterpret_cast<const f32x4*>(s1 + 64 * h);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) a32[((64 * h + q + t) * kLda >> 1) + pw] = pack_bf16(x0[t], x1[t]);
     }
   }
   __syncthreads();
-  bf16x8 fb[kFeatBlock / 16];
-#pragma unroll
-  for (int ft = 0; ft < kFeatBlock / 16; ++ft)
-    fb[ft] = *reinterpret_cast<const bf16x8*>(
-        &At[(16 * ft + (lane & 15)) * kLda + 8 * ((lane >> 4) ^ (ft & 3))]);
-  // Per feature tile the wave's 16 features x 16 per units go through its own
-  // LDS rows (pitch 16 kMaxHidden / 64 + 4 words, so the 16 features' 16-byte
-  // writes fall on distinct banks), and are stored as whole 64 per-byte pieces
-  // of each G row: 4 per lanes per row, 64 / (4 per) rows per store
-  // (measured: 52.8 against 55.3 us with each store writing 64-byte pieces
-  // of 16 rows straight from the accumulators).
-  constexpr int kPitch = 16 * (kMaxHidden / 64) + 4;
-  __shared__ __attribute__((aligned(16))) float Stg[4][16 * kPitch];
-  float* st = Stg[wave];
-  const int rowlanes = 4 * per;                 // lanes per feature row (16 B each)
-  const int rows_per = 64 / rowlanes;           // feature rows per store instruction
-  float* g = G + (int64_t)slot * d.ld + (int64_t)f0 * H + 16 * per * wave;
-#pragma unroll
-  for (int ft = 0; ft < kFeatBlock / 16; ++ft) {
-#pragma unroll
-    for (int u = 0; u < kMaxHidden / 64; ++u) {
-      if (u >= per) break;
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[u], fb[ft], acc, 0, 0, 0);
-      *reinterpret_cast<f32x4*>(st + (lane & 15) * kPitch + 16 * u + 4 * (lane >> 4)) = acc;
+  int buf = 0;
+  for (int blk = blk0; blk < nb; blk += step, buf ^= 1) {
+    if (blk + step < nb) {
+      x0 = *reinterpret_cast<const f32x4*>(s0 + (blk + step) * kFeatBlock);
+      x1 = *reinterpret_cast<const f32x4*>(s1 + (blk + step) * kFeatBlock);
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int r0 = 0; r0 < 16; r0 += rows_per) {
-      const int fr = r0 + lane / rowlanes, cq = lane % rowlanes;
-      if (lane < rows_per * rowlanes && fr < 16) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(st + fr * kPitch + 4 * cq);
-        *reinterpret_cast<f32x4*>(g + (int64_t)(16 * ft + fr) * H + 4 * cq) = v;
+    if (busy) {
+      // group 2 pair of feature 4 g + t, and once swapped both groups of two features
+      float* o = gr + (int64_t)blk * kFeatBlock * H + 128 * pair + 4 * i;
+#pragma unroll 1
+      for (int ft = part; ft < kFeatBlock / 16; ft += parts) {
+        const int f = 16 * ft + i;
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(&At[buf * kFeatBlock * kBatch + f * kBatch + 8 * (g ^ aswz(f))]);
+        f32x4 acc[2][4];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[q][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, dz[q][j], (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+        }
+        if (two) {
+          float* o2 = o + 64 * (g & 1);
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            f32x4 lo, hi;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const float a0 = acc[0][j][t], a1 = acc[1][j][t];
+              const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a0), __float_as_uint(a1), false, false);
+              const uint32_t r0 = r[0], r1 = r[1];
+              lo[j] = __uint_as_float(r0);
+              hi[j] = __uint_as_float(r1);
+            }
+            const int fl = 16 * ft + 4 * (g & 2) + t;  // lanes 0-31: features t, 32-63: 8 + t
+            *reinterpret_cast<f32x4*>(o2 + (int64_t)fl * H) = lo;
+            *reinterpret_cast<f32x4*>(o2 + (int64_t)(fl + 4) * H) = hi;
+          }
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            *reinterpret_cast<f32x4*>(o + (int64_t)(16 * ft + 4 * g + t) * H) =
+                (f32x4){acc[0][0][t], acc[0][1][t], acc[0][2][t], acc[0][3][t]};
+        }
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (blk + step < nb) {
+      stage_x(buf ^ 1);
+      __syncthreads();
+    }
   }
 }
 
@@ -635,7 +659,6 @@ __global__ void __launch_bounds__(256)
 
 struct Workspace {
   int32_t* idx;
-  __bf16* dz1t;
   float* part;        // partial Z1 of each d_in slice
   int64_t part_stride;
 };
@@ -645,8 +668,7 @@ Workspace carve(void* ws, const Dims& d, int64_t rows) {
   Workspace w;
   w.idx = reinterpret_cast<int32_t*>(p);
   p += up256((size_t)rows * 4);
-  w.dz1t = reinterpret_cast<__bf16*>(p);
-  p += up256((size_t)rows * d.hidden * 2);
+  p += up256((size_t)rows * d.hidden * 2);  // unused (workspace_for)
   w.part = reinterpret_cast<float*>(p);
   w.part_stride = (int64_t)(up256((size_t)rows * d.hidden * 4) / 4);
   return w;
@@ -763,11 +785,12 @@ void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_
     hipLaunchKernelGGL(k_mlp_fwd<false>, fgrid, dim3(64 * kFwWaves), 0, st, X, data, w.idx, w.part,
                        w.part_stride, d, K, none);
   }
-  hipLaunchKernelGGL(k_mlp_head<BACKWARD>, dim3(items.count), dim3(kHeadThreads), 0, st, X, w.idx,
-                     labels, w.part, w.part_stride, K.S, w.dz1t, G, losses, d, items);
-  if (BACKWARD)
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3(items.count, d.d_in / kFeatBlock), dim3(256), 0, st, data,
-                       w.idx, w.dz1t, G, d, items);
+  // entries rounded up to whole rounds of XCDs: an entry's workgroups share an L2
+  const int entries = (count + 7) / 8 * 8, blocks = d.d_in / kFeatBlock;
+  const int each = std::min(kBackBlocks, (blocks * entries + kBackGrid - 1) / kBackGrid);
+  hipLaunchKernelGGL(k_mlp_back<BACKWARD>, dim3(entries, BACKWARD ? (blocks + each - 1) / each : 1),
+                     dim3(kBackThreads), 0, st, X, data, w.idx, labels, w.part, w.part_stride, K.S, G,
+                     losses, d, items);
 }
 
 }  // namespace

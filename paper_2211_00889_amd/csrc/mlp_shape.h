@@ -13,7 +13,7 @@ namespace nbsgd {
 constexpr int kBatch = 32;        // mini-batch size (the MFMA K of dW1)
 constexpr int kMaxHidden = 512;
 constexpr int kMaxClasses = 16;   // classes fill one 16-wide MFMA tile
-constexpr int kFeatBlock = 128;   // d_in features per dW1 workgroup
+constexpr int kFeatBlock = 128;   // d_in features staged at a time for dW1
 constexpr int kSkMaxSlices = 4;   // largest split of d_in in the forward GEMM
 
 struct Dims {
@@ -30,9 +30,10 @@ nbsgd_status check_shape(const nbsgd_mlp_shape* s, Dims* d);
 // Bytes rounded up to a multiple of 256.
 inline size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Workspace of a call processing `rows` sample rows: the sample list, dZ1
-// [rows/32][hidden][32] bf16 and kSkMaxSlices partial Z1 planes
-// [rows][hidden] fp32, each 256-byte aligned.
+// Workspace of a call processing `rows` sample rows: the sample list, room for
+// [rows][hidden] bf16 that the kernels no longer use (the size is what callers
+// allocate by, and it stays) and kSkMaxSlices partial Z1 planes [rows][hidden] fp32,
+// each 256-byte aligned.
 inline size_t workspace_for(const Dims& d, int64_t rows) {
   return up256((size_t)rows * 4) + up256((size_t)rows * d.hidden * 2) +
          (size_t)kSkMaxSlices * up256((size_t)rows * d.hidden * 4);

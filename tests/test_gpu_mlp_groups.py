@@ -1,7 +1,9 @@
 """The MLP calls over groups of mini-batches large enough to change how the
 forward splits d_in (1, 2, 3 or 4 slices, by the number of output tiles), and
 quads with 1-4 mini-batches: every loss against the same batch evaluated by
-itself, and sampled ones against the oracle."""
+itself, and sampled ones against the oracle.  And gradients whose workgroups take
+one, several or unequal numbers of feature blocks, with every number of unit
+groups: sampled mini-batches against the oracle, every loss too."""
 
 import numpy as np
 import pytest
@@ -10,6 +12,7 @@ import oracle
 from oracle.mlp import BF16, Shape
 from paper_2211_00889_amd import _lib
 from synth import mlp_data
+from tests.test_gpu_mlp import _grad_ok
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -58,3 +61,46 @@ def test_losses_of_large_groups(d_in, hidden, batches):
     for k in (0, batches // 2, batches - 1):
         _, loss = oracle.mlp.grad(x0, A[idx[k]], y[idx[k]], s, BF16)
         assert abs(w[k] - loss) <= TOL_BF16 * abs(loss), k
+
+
+@pytest.mark.parametrize("d_in,hidden,classes,n,m", [
+    (1408, 448, 16, 4, 16),  # 11 feature blocks by threes, a lone last unit group of 7
+    (2176, 256, 3, 3, 16),   # 17 blocks by fours, 4 unit groups
+    (640, 384, 10, 8, 15),   # 5 blocks in two workgroups, 6 unit groups, two idle waves
+    (1024, 64, 5, 16, 20),   # 8 blocks by sixes (the most), one unit group for 8 waves
+    (128, 320, 10, 1, 2),    # one block
+])
+def test_gradients_of_large_groups(d_in, hidden, classes, n, m):
+    n_samples = 700
+    dims = (d_in, hidden, classes)
+    A = mlp_data.inputs(5, n_samples, d_in)
+    y = mlp_data.teacher_labels(5, A, hidden, classes)
+    x0 = mlp_data.student_init(5, d_in, hidden, classes)
+    rng = np.random.default_rng(d_in + hidden)
+    P = _lib.mlp_param_count(*dims)
+    X = np.zeros((n, P), np.float32)
+    X[:, :x0.size] = x0 + 0.05 * rng.standard_normal((n, x0.size)).astype(np.float32)
+    mask = np.ones((n, m), np.uint8)
+    mask[n - 1, m // 2] = 0
+    idx = rng.integers(0, n_samples, size=(n, m, 32)).astype(np.int32)
+    data, labels = torch.from_numpy(A).to(DEV), torch.from_numpy(y.astype(np.int32)).to(DEV)
+    G = torch.full((n, m, P), 7.0, dtype=torch.float32, device=DEV)
+    losses = torch.full((n * m,), -1.0, dtype=torch.float32, device=DEV)
+    ws = torch.empty((_lib.mlp_workspace_bytes(*dims, n * m * 32) + 15) // 16 * 4,
+                     dtype=torch.float32, device=DEV)
+    print(f"[case] gradients d_in={d_in} hidden={hidden} classes={classes} n={n} m={m}", flush=True)
+    _lib.mlp_grad(torch.from_numpy(X).to(DEV), m, dims, data, labels, idx, mask, G, losses, ws)
+    torch.cuda.synchronize()
+    Lh = losses.cpu().numpy().reshape(n, m)
+    s = Shape(d_in, hidden, classes, 32)
+    assert (G[n - 1, m // 2] == 7.0).all() and Lh[n - 1, m // 2] == -1.0
+    for i, j in {(0, 0), (n // 2, m - 1), (n - 1, 0), (n - 1, m - 1)} - {(n - 1, m // 2)}:
+        prm, b = X[i, :s.n_params], idx[i, j]
+        g = G[i, j].cpu().numpy()
+        assert _grad_ok(g, prm, A[b], y[b], s, dims), (i, j)
+        assert (g[s.n_params:] == 0).all()
+    for i in range(n):
+        for j in range(m):
+            if mask[i, j] and (i + j) % 5 == 0:
+                _, loss = oracle.mlp.grad(X[i, :s.n_params], A[idx[i, j]], y[idx[i, j]], s, BF16)
+                assert abs(Lh[i, j] - loss) <= TOL_BF16 * abs(loss), (i, j)
