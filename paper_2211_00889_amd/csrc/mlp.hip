@@ -37,6 +37,8 @@ namespace {
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
@@ -93,9 +95,56 @@ __device__ __forceinline__ bf16x8 to_bf16(f32x4 lo, f32x4 hi) {
                                  bf16x8);
 }
 
-// Writes the sample index of every row of the chunk's list entries (used
-// when a group's indices do not fit the forward kernel's arguments).
-__global__ void __launch_bounds__(256) k_put_idx(int32_t* __restrict__ dst, IdxChunk c) {
+// Orders the wave's LDS writes before its later LDS accesses (other lanes' data).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Swizzle of row r of a 16-row tile of the forward's LDS: within rows 0-7 and
+// within 8-15 all eight values differ (writes), and so they do within the even and
+// the odd rows, in pairs 2 v, 2 v + 1 for rows 0-3 and 12-15 (reads).
+__device__ __forceinline__ int fwd_swizzle(int r) {
+  return ((r & 4) | (r & 1) << 1 | ((r >> 1) & 1)) ^ (r & 8 ? 6 : 0);
+}
+
+// W1 of the present learners in bf16, as the forward's LDS holds it: tile (learner
+// k, unit block, chunk), chunks fastest, is the image [unit row][64 k] of 128 units.
+constexpr int kFwUnits = 128, kFwKc = 64, kFwTile = kFwUnits * kFwKc;
+struct Pack {
+  const float* X;
+  __bf16* w1;
+  int64_t ld;
+  int32_t hidden, chunks, ub;
+  int32_t idx_blocks;    // workgroups before the first tile's
+  uint32_t learner[4];   // as SkMap's
+};
+static_assert(sizeof(IdxChunk) + sizeof(Pack) + 32 <= 4096, "kernel arguments exceed 4 KiB");
+
+// Writes the sample index of every row of the chunk's list entries (used when a
+// group's indices do not fit the forward kernel's arguments); workgroups from
+// p.idx_blocks on write one tile of the packed W1 each, a thread 8 k x 4 units.
+__global__ void __launch_bounds__(256) k_put_idx(int32_t* __restrict__ dst, IdxChunk c, Pack p) {
+  if ((int)blockIdx.x >= p.idx_blocks) {  // uniform
+    const int tile = blockIdx.x - p.idx_blocks;
+    const int chunk = tile % p.chunks, ubk = tile / p.chunks % p.ub, li = tile / p.chunks / p.ub;
+    const int learner = (int)((p.learner[li >> 2] >> (8 * (li & 3))) & 0xffu);
+    const int wq = threadIdx.x & 31, o = threadIdx.x >> 5, H = p.hidden, u0 = kFwUnits * ubk;
+    // unit quads past the block read its first units; nothing stores what they give
+    const float* src = p.X + (int64_t)learner * p.ld + (int64_t)(kFwKc * chunk + 8 * o) * H + u0 +
+                       (u0 + 4 * wq < H ? 4 * wq : 0);
+    f32x4 v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = *reinterpret_cast<const f32x4*>(src + (int64_t)r * H);
+    __bf16* out = p.w1 + (int64_t)tile * kFwTile + (64 * (wq >> 4) + (wq & 15)) * kFwKc +
+                  8 * (o ^ fwd_swizzle(wq & 15));
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      *reinterpret_cast<bf16x8*>(out + 16 * t * kFwKc) = to_bf16(
+          (f32x4){v[0][t], v[1][t], v[2][t], v[3][t]}, (f32x4){v[4][t], v[5][t], v[6][t], v[7][t]});
+    return;
+  }
   const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= c.n_slots * kBatch) return;
   const int32_t v = c.wide ? (int32_t)c.v[t] : (int32_t)((c.v[t >> 1] >> (16 * (t & 1))) & 0xffffu);
@@ -131,8 +180,13 @@ __global__ void __launch_bounds__(256) k_put_idx(int32_t* __restrict__ dst, IdxC
 // time (4,096 samples: 200 MB of reads past the L2s with the unit blocks a round
 // apart, 75 MB so).  INLINE: the sample indices come from the kernel arguments
 // and the workgroups of slice 0 and unit block 0 copy them to the workspace for
-// the later kernels; otherwise they are read from the workspace.
-constexpr int kFwWaves = 8, kFwMb = 4, kFwUnits = 128, kFwKc = 64;
+// the later kernels; otherwise they are read from the workspace.  PACKED: W1 comes
+// from the workspace in bf16, tile by tile as LDS holds it (k_put_idx packed it), and
+// is staged as it is: half the bytes through the L2s and L1s, which deliver 128 KiB
+// a chunk step to every CU without it, and no conversion in each of the quads
+// (4,096 samples 31.3 -> 28 us in the trace; a second chunk of samples loaded ahead
+// on top changed nothing).
+constexpr int kFwWaves = 8, kFwMb = 4;
 struct SkMap {
   int32_t n;              // learners present
   int32_t S;              // K slices
@@ -142,27 +196,13 @@ struct SkMap {
   int32_t first[17];      // first list entry of each learner (first[n] = count)
 };
 static_assert(NBSGD_MAX_LEARNERS <= 16, "SkMap holds at most 16 learners");
-static_assert(sizeof(InlineIdx) + sizeof(Dims) + sizeof(SkMap) + 5 * 8 <= 4096,
+static_assert(sizeof(InlineIdx) + sizeof(Dims) + sizeof(SkMap) + 6 * 8 <= 4096,
               "kernel arguments exceed 4 KiB");
 
-// Orders the wave's LDS writes before its later LDS accesses (other lanes' data).
-__device__ __forceinline__ void wave_lds_fence() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Swizzle of row r of a 16-row tile: within rows 0-7 and within 8-15 all eight
-// values differ (writes), and so they do within the even and the odd rows, in
-// pairs 2 v, 2 v + 1 for rows 0-3 and 12-15 (reads).
-__device__ __forceinline__ int fwd_swizzle(int r) {
-  return ((r & 4) | (r & 1) << 1 | ((r >> 1) & 1)) ^ (r & 8 ? 6 : 0);
-}
-
-template <bool INLINE>
+template <bool INLINE, bool PACKED>
 __global__ void __launch_bounds__(64 * kFwWaves, 2)
-    k_mlp_fwd(const float* __restrict__ X, const float* __restrict__ data,
-              int32_t* __restrict__ idx, float* __restrict__ Zpart, int64_t part_stride, Dims d,
+    k_mlp_fwd(const float* __restrict__ X, const __bf16* __restrict__ w1,
+              const float* __restrict__ data, int32_t* __restrict__ idx, float* __restrict__ Zpart, int64_t part_stride, Dims d,
               SkMap M, Idx16<INLINE ? kInline * kBatch / 2 : 1> I) {
   constexpr int UB = kFwUnits, KC = kFwKc;
   __shared__ __attribute__((aligned(16))) __bf16 Ws[2][2][UB * KC];
@@ -219,7 +259,11 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
                     (4 * wq < units ? 4 * wq : 0);
   const int wofs = (64 * (wq >> 4) + (wq & 15)) * KC + 8 * (wave ^ fwd_swizzle(wq & 15)) + 4 * half;
 
+  // packed W1: 16 bytes of each 8 KiB of a tile
+  const __bf16* pp = w1 + (int64_t)(li * M.ub + ubk) * T * kFwTile + 8 * tid;
+
   f32x4 a[2][KC / 16], w[2][4];
+  u32x4 wb[2][2];
   const int na = kh ? n1 : n0;  // this wave's chunks
   auto load_a = [&](int c) {
     c = min(c, na - 1);
@@ -232,18 +276,31 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int k = kc[h] + min(c, (h ? n1 : n0) - 1);
+      if constexpr (PACKED) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) w[h][r] = *reinterpret_cast<const f32x4*>(wp + (int64_t)(k * KC + r) * H);
+        for (int r = 0; r < 2; ++r)
+          wb[h][r] = *reinterpret_cast<const u32x4*>(pp + (int64_t)k * kFwTile + r * (kFwTile / 2));
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[h][r] = *reinterpret_cast<const f32x4*>(wp + (int64_t)(k * KC + r) * H);
+      }
     }
   };
   auto stage_w = [&](int buf) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < 2; ++h) {
+      if constexpr (PACKED) {
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint2 v = {pack_bf16(w[h][0][t], w[h][1][t]), pack_bf16(w[h][2][t], w[h][3][t])};
-        *reinterpret_cast<uint2*>(&Ws[buf][h][wofs + 16 * t * KC]) = v;
+        for (int r = 0; r < 2; ++r)
+          *reinterpret_cast<u32x4*>(&Ws[buf][h][r * (kFwTile / 2) + 8 * tid]) = wb[h][r];
+      } else {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const uint2 v = {pack_bf16(w[h][0][t], w[h][1][t]), pack_bf16(w[h][2][t], w[h][3][t])};
+          *reinterpret_cast<uint2*>(&Ws[buf][h][wofs + 16 * t * KC]) = v;
+        }
       }
+    }
   };
   __bf16* aw = As[wave];
   auto stage_a = [&]() {
@@ -659,6 +716,8 @@ __global__ void __launch_bounds__(kBackThreads, 4)
 
 struct Workspace {
   int32_t* idx;
+  __bf16* w1;         // packed W1, where it fits
+  size_t w1_bytes;
   float* part;        // partial Z1 of each d_in slice
   int64_t part_stride;
 };
@@ -668,7 +727,9 @@ Workspace carve(void* ws, const Dims& d, int64_t rows) {
   Workspace w;
   w.idx = reinterpret_cast<int32_t*>(p);
   p += up256((size_t)rows * 4);
-  p += up256((size_t)rows * d.hidden * 2);  // unused (workspace_for)
+  w.w1 = reinterpret_cast<__bf16*>(p);
+  w.w1_bytes = up256((size_t)rows * d.hidden * 2);
+  p += w.w1_bytes;
   w.part = reinterpret_cast<float*>(p);
   w.part_stride = (int64_t)(up256((size_t)rows * d.hidden * 4) / 4);
   return w;
@@ -688,9 +749,9 @@ nbsgd_status check_idx(const int32_t* host, const int32_t* slots, int n_slots, i
 
 // Copies the sample indices of list entries 0 .. count-1 (host idx[slot*32 ..]
 // of entry e's slot mb[e].second) to the workspace rows e*32 .. through the
-// kernel arguments of k_put_idx.
+// kernel arguments of k_put_idx; its first launch also packs `tiles` tiles of W1.
 void put_idx(const int32_t* host, const std::pair<int, int>* mb, int count, bool wide,
-             const Workspace& w, hipStream_t s) {
+             const Workspace& w, Pack pack, int tiles, hipStream_t s) {
   const int per = wide ? kUpSlots / 2 : kUpSlots;
   for (int k0 = 0; k0 < count; k0 += per) {
     IdxChunk c;
@@ -706,7 +767,9 @@ void put_idx(const int32_t* host, const std::pair<int, int>* mb, int count, bool
         else c.v[t >> 1] |= (uint32_t)src[r] << (16 * (t & 1));
       }
     }
-    hipLaunchKernelGGL(k_put_idx, dim3((c.n_slots * kBatch + 255) / 256), dim3(256), 0, s, w.idx, c);
+    pack.idx_blocks = (c.n_slots * kBatch + 255) / 256;
+    hipLaunchKernelGGL(k_put_idx, dim3(pack.idx_blocks + (k0 ? 0 : tiles)), dim3(256), 0, s, w.idx, c,
+                       pack);
   }
 }
 
@@ -723,21 +786,40 @@ uint32_t item(int learner, int slot) { return ((uint32_t)learner << 24) | ((uint
 // the fewer slices on a tie, since every slice adds a plane of partial sums that is
 // written and read (4,096 samples, 128 tiles, 2 slices: 43.3 us a call; 256-row
 // blocks in 4 slices 45.6; the 8 x 8 workload's 50 tiles take 4).
-int fwd_slices(int d_in, int tiles) {
+// *steps: that least, the chunk steps that a CU makes.
+int fwd_slices(int d_in, int tiles, int* steps) {
   const int T = d_in / kFwKc;
-  int best = 0, least = 0;
+  int best = 0;
   for (int q = 1; q <= kSkMaxSlices && 2 * q <= T; ++q) {
     const int cost = (tiles * q + 255) / 256 * ((T + 2 * q - 1) / (2 * q));
-    if (!best || cost < least) best = q, least = cost;
+    if (!best || cost < *steps) best = q, *steps = cost;
   }
   return best;
+}
+
+// Chunk steps of a CU from which the forward reads W1 packed: a step saves 0.2-0.4
+// us, packing adds 1-1.5 us to a launch that is there anyway (a group whose indices
+// go inline has none and is never packed).  mlp_loss, 32-sample batches x d_in x
+// hidden, packed against not, other samples in each call: 512 x 3072x512 (48 steps)
+// 130.4 and 147.9 us, 256 x 3072x512 (24) 72.4 and 83.3, 128 x 3072x512 (12) 46.8 and
+// 50.8, 96 x 3072x384 (8) 35.8 and 37.6; the same samples each time: 80 x 2560x448 (7)
+// 30.6 and 30.3, 40 x 1152x512 (3) 24.7 and 23.8; gradients of 8 x 16 mini-batches
+// 384x512 (3) 40.7 and 39.8.
+constexpr int kPackSteps = 8;
+
+// Tiles of W1 that the forward of this group reads packed; 0 where it does not, or
+// where they would not fit their part of the workspace.
+int pack_tiles(const SkMap& K, const Dims& d, int steps, const Workspace& w) {
+  const int tiles = K.n * K.ub * (d.d_in / kFwKc);
+  return steps >= kPackSteps && (size_t)tiles * kFwTile * sizeof(__bf16) <= w.w1_bytes ? tiles : 0;
 }
 
 // Launches the kernels over mini-batches `mb` (learner, slot), sorted by
 // learner, of one group (at most kMaxList): the sample indices host_idx[slot
 // * 32 ..] (checked) go to the workspace in the forward kernel's arguments
 // when the group has at most kInline mini-batches and they fit 16 bits
-// (`wide` false), otherwise through k_put_idx first.
+// (`wide` false), otherwise through k_put_idx first, which also packs W1 for long
+// forwards.
 template <bool BACKWARD>
 void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_idx, bool wide,
                   const float* X, const float* data, const int32_t* labels, const Workspace& w,
@@ -760,7 +842,8 @@ void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_
   K.first[K.n] = items.count;
   int tiles = 0;
   for (int k = 0; k < K.n; ++k) tiles += K.ub * ((K.first[k + 1] - K.first[k] + kFwMb - 1) / kFwMb);
-  K.S = fwd_slices(d.d_in, tiles);
+  int steps = 0;
+  K.S = fwd_slices(d.d_in, tiles, &steps);
   for (int k = 0; k < K.n; ++k) {
     K.off[k] = sk_total;
     sk_total += K.S * K.ub * ((K.first[k + 1] - K.first[k] + kFwMb - 1) / kFwMb);
@@ -777,12 +860,23 @@ void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_
         I.v[t >> 1] |= (uint32_t)src[r] << (16 * (t & 1));
       }
     }
-    hipLaunchKernelGGL(k_mlp_fwd<true>, fgrid, dim3(64 * kFwWaves), 0, st, X, data, w.idx, w.part,
+    hipLaunchKernelGGL((k_mlp_fwd<true, false>), fgrid, dim3(64 * kFwWaves), 0, st, X, w.w1, data, w.idx, w.part,
                        w.part_stride, d, K, I);
   } else {
-    put_idx(host_idx, mb, count, wide, w, st);
+    const int pk = pack_tiles(K, d, steps, w);
+    Pack pack;
+    memset(&pack, 0, sizeof pack);
+    pack.X = X;
+    pack.w1 = w.w1;
+    pack.ld = d.ld;
+    pack.hidden = d.hidden;
+    pack.chunks = d.d_in / kFwKc;
+    pack.ub = K.ub;
+    memcpy(pack.learner, K.learner, sizeof pack.learner);
+    put_idx(host_idx, mb, count, wide, w, pack, pk, st);
     const Idx16<1> none = {{0u}};
-    hipLaunchKernelGGL(k_mlp_fwd<false>, fgrid, dim3(64 * kFwWaves), 0, st, X, data, w.idx, w.part,
+    hipLaunchKernelGGL((pk ? k_mlp_fwd<false, true> : k_mlp_fwd<false, false>), fgrid,
+                       dim3(64 * kFwWaves), 0, st, X, w.w1, data, w.idx, w.part,
                        w.part_stride, d, K, none);
   }
   // entries rounded up to whole rounds of XCDs: an entry's workgroups share an L2

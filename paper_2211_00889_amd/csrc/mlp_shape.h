@@ -31,8 +31,8 @@ nbsgd_status check_shape(const nbsgd_mlp_shape* s, Dims* d);
 inline size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 // Workspace of a call processing `rows` sample rows: the sample list, room for
-// [rows][hidden] bf16 that the kernels no longer use (the size is what callers
-// allocate by, and it stays) and kSkMaxSlices partial Z1 planes [rows][hidden] fp32,
+// [rows][hidden] bf16 (the packed W1 of the learners present, where it fits; the
+// size is what callers allocate by, and it stays) and kSkMaxSlices partial Z1 planes [rows][hidden] fp32,
 // each 256-byte aligned.
 inline size_t workspace_for(const Dims& d, int64_t rows) {
   return up256((size_t)rows * 4) + up256((size_t)rows * d.hidden * 2) +
