@@ -622,8 +622,10 @@ __global__ void __launch_bounds__(kBackThreads, 4)
         h[t] = *reinterpret_cast<const uint2*>(Hs + (4 * g + (t & 3) + 16 * (t >> 2)) * kLdh + ub);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        // B[class][unit]; classes 16-31 multiply the zeros of fz
-        const bf16x8 fw = *reinterpret_cast<const bf16x8*>(W2s + (ub + j) * kMaxClasses + 8 * (g & 1));
+        // B[class][unit]; classes 16-31 are zero on both sides (a zero of fz alone
+        // would make an infinite weight NaN)
+        bf16x8 fw = *reinterpret_cast<const bf16x8*>(W2s + (ub + j) * kMaxClasses + 8 * (g & 1));
+        if (g > 1) fw = (bf16x8)((__bf16)0.0f);
         f32x4 v[2];
         float db1 = 0.0f;
 #pragma unroll

@@ -633,3 +633,38 @@ def test_loss_odd_batch_count(tiny):
     got = out.cpu().numpy()
     want = [oracle.mlp.forward(x0, A[idx[k:k + 32]], y[idx[k:k + 32]], s, BF16)[0] for k in (0, 32, 64)]
     np.testing.assert_allclose(got, want, rtol=TOL_BF16)
+
+
+def test_gradient_of_an_infinite_weight_is_infinite_not_nan():
+    """A weight W2[u][c] of -inf (given so, or beyond the largest bf16) on samples of
+    class c: the loss is +inf, dZ2 stays finite, and unit u's dZ1 is +inf in every
+    row where it is active.  The zero-padded classes of that product must not add
+    0 * inf.  Positive samples keep dW1's sums of infinities of one sign."""
+    dims = (128, 64, 10)
+    s = Shape(*dims, 32)
+    A = np.abs(mlp_data.inputs(4, 64, dims[0])) + np.float32(0.01)
+    c, u = 3, 21
+    y = np.full(64, c, np.int32)
+    prm = mlp_data.student_init(4, *dims).astype(np.float32)
+    _, o_b1, o_w2, _ = s.offsets()
+    prm[o_b1 + u] = 50.0  # active on every sample
+    P = _lib.mlp_param_count(*dims)
+    idx = np.arange(32, dtype=np.int32).reshape(1, 1, 32)
+    data, labels = torch.from_numpy(A).to(DEV), torch.from_numpy(y).to(DEV)
+    ws = torch.empty((_lib.mlp_workspace_bytes(*dims, 32) + 15) // 16 * 4, dtype=torch.float32, device=DEV)
+    for value in (-np.inf, -3.4e38):
+        prm[o_w2 + u * dims[2] + c] = value
+        _say(f"mlp grad, W2[{u}][{c}] = {value}")
+        G = torch.full((1, 1, P), 7.0, dtype=torch.float32, device=DEV)
+        losses = torch.zeros(1, dtype=torch.float32, device=DEV)
+        _lib.mlp_grad(torch.from_numpy(pad_cols(prm[None], P)).to(DEV), 1, dims, data, labels, idx,
+                      np.ones((1, 1), np.uint8), G, losses, ws)
+        g = G[0, 0].cpu().numpy()
+        assert losses.item() == np.inf
+        dW1 = g[:dims[0] * dims[1]].reshape(dims[0], dims[1])
+        assert g[o_b1 + u] == np.inf and (dW1[:, u] == np.inf).all()
+        rest = np.delete(np.arange(dims[1]), u)
+        assert np.isfinite(g[o_b1 + rest]).all() and np.isfinite(dW1[:, rest]).all()
+        with np.errstate(over="ignore"):
+            want, _ = oracle.mlp.grad(prm, A[:32], y[:32], s, BF16)
+        assert np.array_equal(np.isposinf(want), np.isposinf(g[:s.n_params]))
