@@ -29,6 +29,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "mlp_plan.h"
 #include "mlp_shape.h"
 
 using namespace nbsgd;
@@ -417,11 +418,6 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
 // step, which reads from the last column, finds the newest in the memory-side
 // cache (a contiguous range per workgroup: 97.1 against 95.9 us, and a slower step).
 constexpr int kBackThreads = 512, kBackWaves = kBackThreads / 64;
-// workgroups that take one entry's features: as many as keep the launch within one
-// workgroup per CU, since the head costs each of them 10 us, but at most six blocks
-// each (8 x 4 mini-batches 3072x512: 62.6 us so, 64.1 with two per CU; 12 x 8 of
-// 1408x512 79.9 and 82.5; 16 x 16 373.4 and 371.2 with at most four)
-constexpr int kBackGrid = 256, kBackBlocks = 6;
 
 template <bool BACKWARD>
 __global__ void __launch_bounds__(kBackThreads, 4)
@@ -881,9 +877,8 @@ void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_
                        dim3(64 * kFwWaves), 0, st, X, w.w1, data, w.idx, w.part,
                        w.part_stride, d, K, none);
   }
-  // entries rounded up to whole rounds of XCDs: an entry's workgroups share an L2
-  const int entries = (count + 7) / 8 * 8, blocks = d.d_in / kFeatBlock;
-  const int each = std::min(kBackBlocks, (blocks * entries + kBackGrid - 1) / kBackGrid);
+  const int entries = back_entries(count), blocks = d.d_in / kFeatBlock;
+  const int each = back_blocks(blocks, entries);
   hipLaunchKernelGGL(k_mlp_back<BACKWARD>, dim3(entries, BACKWARD ? (blocks + each - 1) / each : 1),
                      dim3(kBackThreads), 0, st, X, data, w.idx, labels, w.part, w.part_stride, K.S, G,
                      losses, d, items);
