@@ -346,7 +346,9 @@ nbsgd_status nbsgd_minibatch_indices(uint64_t seed, uint64_t step, int32_t n, in
  *                idx[i][j][:] at parameters X[i], for mask[i*m+j] != 0;
  *   losses[i*m+j] = that mean loss.
  * The padding entries of a finished row are set to 0.  Unfinished rows of G
- * and entries of losses are left untouched.  Every GEMM
+ * and entries of losses are left untouched.  A mini-batch's gradient and loss
+ * depend on its samples, labels and replica alone, bit for bit: not on which
+ * or how many other mini-batches the call has.  Every GEMM
  * input (the samples, W1, bf16(ReLU(Z1)), W2, dZ2, dZ1) is rounded to bf16
  * (nearest even) and multiplied on the matrix cores with fp32 accumulation;
  * bias, ReLU, softmax and cross-entropy are fp32.
@@ -404,7 +406,8 @@ nbsgd_status nbsgd_mlp_grad_noalloc(const float *X, int64_t ld, int32_t n, int32
 
 /* Mean cross-entropy of one parameter vector on `count` samples, in batches
  * of 32: losses[k] = mean loss of samples idx[32k .. 32k+31] (same precision
- * as nbsgd_mlp_grad's forward pass).  Used to evaluate the average of the
+ * as nbsgd_mlp_grad's forward pass, and like there independent of the call's
+ * other batches, bit for bit).  Used to evaluate the average of the
  * replicas, the method's output (Alg. 1/2 output line).
  * params device fp32 [P]; idx host int32 [count], count a multiple of 32 and
  * at most 16384; losses device fp32 [count / 32].

@@ -7,7 +7,8 @@
 // conversion) and multiplied with fp32 accumulation:
 //   k_mlp_fwd    partial Z1 = A W1 over one slice of d_in, per 128-row x
 //                128-unit tile, on MFMA 16x16x32 (both operands staged in LDS)
-//   k_mlp_back   per mini-batch: Z1 = sum of the slices + b1, H =
+//   k_mlp_back   per mini-batch: Z1 = sum of the slices (in an order that does not
+//                depend on their number) + b1, H =
 //                bf16(relu(Z1)), logits = H W2 + b2 (MFMA, classes padded to
 //                16), softmax-CE, the loss; and for gradients dZ2, dZ1 = (dZ2
 //                W2^T) * [Z1 > 0], db1, dW2 = H^T dZ2, db2 and dW1 = A^T dZ1
@@ -112,7 +113,7 @@ __device__ __forceinline__ int fwd_swizzle(int r) {
 
 // W1 of the present learners in bf16, as the forward's LDS holds it: tile (learner
 // k, unit block, chunk), chunks fastest, is the image [unit row][64 k] of 128 units.
-constexpr int kFwUnits = 128, kFwKc = 64, kFwTile = kFwUnits * kFwKc;
+constexpr int kFwUnits = 128, kFwTile = kFwUnits * kFwKc;
 struct Pack {
   const float* X;
   __bf16* w1;
@@ -153,12 +154,13 @@ __global__ void __launch_bounds__(256) k_put_idx(int32_t* __restrict__ dst, IdxC
 }
 
 // Forward, split over d_in.  Work item: a quad (up to four mini-batches of one
-// learner, 128 rows), a block of 128 hidden units and one of S slices of d_in (in
-// chunks of 64, as equal as they go).  Eight waves: wave w takes all 128 units for mini-batch w % 4 over half
-// w / 4 of the slice (2 x 8 accumulators), so that a W1 fragment read from LDS
+// learner, 128 rows), a block of 128 hidden units and one of S slices of d_in (parts
+// and their order: mlp_plan.h).  Eight waves: wave w takes all 128 units for
+// mini-batch w % 4 over side w / 4 of the slice (2 x 8 accumulators, twice that where
+// a side has two leaves), so that a W1 fragment read from LDS
 // feeds two MFMAs and four waves share its staging.  Per chunk of 64 k:
-//   W1  [half][unit][k] in bf16, staged by all waves for all (each thread
-//       transposes a 4 k x 4 unit cell of either half), two buffers, one barrier
+//   W1  [side][unit][k] in bf16, staged by all waves for all (each thread
+//       transposes a 4 k x 4 unit cell of either side), two buffers, one barrier
 //       a chunk; loaded one chunk ahead of its staging
 //   A   the wave's own 32 rows, loaded one chunk ahead with four lanes on 64
 //       contiguous bytes of a row, converted into the wave's own LDS rows and read
@@ -168,12 +170,12 @@ __global__ void __launch_bounds__(256) k_put_idx(int32_t* __restrict__ dst, IdxC
 // Rows are 64 bf16 (128 bytes); octet o of a row is stored at o ^ swizzle(row),
 // which leaves the 8-byte writes (16 lanes a cycle) and the 16-byte fragment reads
 // free of bank conflicts; a 64-unit group's unit 4 q + t is LDS row 16 t + q, so
-// that lane q of a result holds four consecutive units.  The two halves are added
-// through LDS at the end (first half + second half) and the sum goes to slice s
-// of the partial buffer; k_mlp_back adds the slices in slice order.
-// What bounds it: with samples and W1 cold (8 x 8 workload, 73 MB) their fetch, 27-33
-// us; with 4,096 samples of one learner the chunk's chain of staging, LDS reads and
-// MFMAs and the partial sums' write, 26 us (45.8 with 32-row x 64-unit waves,
+// that lane q of a result holds four consecutive units.  The two sides are added
+// through LDS at the end of a pair of parts and the sum goes to slice s of the partial
+// buffer; k_mlp_back adds the slices.
+// What bounds it: with samples and W1 cold (8 x 8 workload, 73 MB) their fetch, 25-29 us;
+// with 4,096 samples of one learner the chunk's chain of staging, LDS reads and
+// MFMAs and the partial sums' write, 26.6 us (45.8 with 32-row x 64-unit waves,
 // both operands staged for all waves and 1/4 slices: twice the partial sums).
 // The work items are split into eight equal ranges, one per XCD (workgroup b runs
 // on XCD b % 8), so the items of one learner share an L2; the unit blocks of a
@@ -185,8 +187,8 @@ __global__ void __launch_bounds__(256) k_put_idx(int32_t* __restrict__ dst, IdxC
 // from the workspace in bf16, tile by tile as LDS holds it (k_put_idx packed it), and
 // is staged as it is: half the bytes through the L2s and L1s, which deliver 128 KiB
 // a chunk step to every CU without it, and no conversion in each of the quads
-// (4,096 samples 31.3 -> 28 us in the trace; a second chunk of samples loaded ahead
-// on top changed nothing).
+// (4,096 samples 31.3 us without it in the trace; a second chunk of samples loaded
+// ahead on top changed nothing).
 constexpr int kFwWaves = 8, kFwMb = 4;
 struct SkMap {
   int32_t n;              // learners present
@@ -200,7 +202,7 @@ static_assert(NBSGD_MAX_LEARNERS <= 16, "SkMap holds at most 16 learners");
 static_assert(sizeof(InlineIdx) + sizeof(Dims) + sizeof(SkMap) + 6 * 8 <= 4096,
               "kernel arguments exceed 4 KiB");
 
-template <bool INLINE, bool PACKED>
+template <bool INLINE, bool PACKED, int PAIRS>
 __global__ void __launch_bounds__(64 * kFwWaves, 2)
     k_mlp_fwd(const float* __restrict__ X, const __bf16* __restrict__ w1,
               const float* __restrict__ data, int32_t* __restrict__ idx, float* __restrict__ Zpart, int64_t part_stride, Dims d,
@@ -208,6 +210,11 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
   constexpr int UB = kFwUnits, KC = kFwKc;
   __shared__ __attribute__((aligned(16))) __bf16 Ws[2][2][UB * KC];
   __shared__ __attribute__((aligned(16))) __bf16 As[kFwWaves][kBatch * KC];
+  // the exchange of sums: W1's buffers, which nothing reads after a slice's last step,
+  // but a slice's first of two pairs ends with the second's first chunk staged
+  __shared__ __attribute__((aligned(16))) float Sums[PAIRS == 2 ? kFwWaves * 16 * UB : 1];
+  float* Ex = PAIRS == 2 ? Sums : reinterpret_cast<float*>(Ws);
+  static_assert(sizeof(Ws) == kFwWaves * 16 * UB * sizeof(float), "an exchange takes W1's buffers");
   const int xcd = blockIdx.x & 7;
   const int64_t total = M.off[M.n];
   const int item = (int)(xcd * total / 8) + (int)(blockIdx.x >> 3);
@@ -224,11 +231,8 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
   const int nmb = min(kFwMb, cnt - kFwMb * quad);
   const int H = d.hidden, u0 = UB * ubk;
   const int units = min(UB, H - u0);
-  // chunks of the slice's halves: [kc[0], kc[1]) and [kc[1], kc[2])
-  const int T = d.d_in / KC;
-  const int kc[3] = {2 * s * T / (2 * M.S), (2 * s + 1) * T / (2 * M.S), (2 * s + 2) * T / (2 * M.S)};
-  const int n0 = kc[1] - kc[0], n1 = kc[2] - kc[1];
-  const int nck = max(n0, n1), nmin = min(n0, n1);  // they differ by at most one
+  const FwdChunks chunks = {d.d_in / KC};
+  const int per = chunks.parts() / M.S;  // parts of a slice
   const int learner = (int)((M.learner[li >> 2] >> (8 * (li & 3))) & 0xffu);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -250,7 +254,7 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
     } else {
       v = idx[t];
     }
-    ap[f] = data + (int64_t)v * d.d_in + kc[kh] * KC + 4 * p;
+    ap[f] = data + (int64_t)v * d.d_in + 4 * p;
   }
   // W1: k 8 wave + 4 half .. +3 of either half's chunk, units 4 wq .. +3; four
   // lanes read 64 contiguous bytes, a load two whole 512-byte row pieces
@@ -261,22 +265,20 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
   const int wofs = (64 * (wq >> 4) + (wq & 15)) * KC + 8 * (wave ^ fwd_swizzle(wq & 15)) + 4 * half;
 
   // packed W1: 16 bytes of each 8 KiB of a tile
-  const __bf16* pp = w1 + (int64_t)(li * M.ub + ubk) * T * kFwTile + 8 * tid;
+  const __bf16* pp = w1 + (int64_t)(li * M.ub + ubk) * chunks.T * kFwTile + 8 * tid;
 
   f32x4 a[2][KC / 16], w[2][4];
   u32x4 wb[2][2];
-  const int na = kh ? n1 : n0;  // this wave's chunks
   auto load_a = [&](int c) {
-    c = min(c, na - 1);
 #pragma unroll
     for (int f = 0; f < 2; ++f)
 #pragma unroll
       for (int q = 0; q < KC / 16; ++q) a[f][q] = *reinterpret_cast<const f32x4*>(ap[f] + c * KC + 16 * q);
   };
-  auto load_w = [&](int c) {
+  auto load_w = [&](int k0, int k1) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int k = kc[h] + min(c, (h ? n1 : n0) - 1);
+      const int k = h ? k1 : k0;
       if constexpr (PACKED) {
 #pragma unroll
         for (int r = 0; r < 2; ++r)
@@ -314,12 +316,15 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
       }
     wave_lds_fence();
   };
-  f32x4 acc[2][UB / 16];
+  f32x4 acc0[2][UB / 16], acc[2][UB / 16];  // of a side's first of two leaves, and of the other or only one
+  auto clear = [&]() {
 #pragma unroll
-  for (int f = 0; f < 2; ++f)
+    for (int f = 0; f < 2; ++f)
 #pragma unroll
-    for (int u = 0; u < UB / 16; ++u) acc[f][u] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto multiply = [&](int buf) {
+      for (int u = 0; u < UB / 16; ++u) acc0[f][u] = acc[f][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
+  auto multiply = [&](int buf, f32x4 (&acc)[2][UB / 16]) {
 #pragma unroll
     for (int ks = 0; ks < KC / 32; ++ks) {
       const int o = 8 * ((4 * ks + g) ^ fwd_swizzle(i));
@@ -335,64 +340,78 @@ __global__ void __launch_bounds__(64 * kFwWaves, 2)
     }
     wave_lds_fence();
   };
-  // chunk indices past the last one are clamped, so that the loads stay
-  // unconditional; set c + 1 is loaded while chunk c is multiplied
-  load_w(0);
-  load_a(0);
-  stage_w(0);
-  load_w(1);
-  __syncthreads();
-  for (int c = 0; c < nmin; ++c) {
-    stage_a();
-    load_a(c + 1);
-    multiply(c & 1);
-    if (c + 1 < nck) {
-      stage_w((c + 1) & 1);
-      load_w(c + 2);
+  // Ends a pair: wave w < 4 keeps row tile 0 and gives row tile 1 to wave w + 4, through
+  // Ex, which the partner reads after a barrier and which is written again a step's
+  // barrier later at the earliest.  The sum of a slice's first pair waits for the
+  // second where this wave read the partner's share of it.
+  f32x4 sum[UB / 64][4];
+  auto add = [&](bool first, bool last) {
+    if constexpr (PAIRS > 0) {
+#pragma unroll
+      for (int f = 0; f < 2; ++f)
+#pragma unroll
+        for (int u = 0; u < UB / 16; ++u) acc[f][u] += acc0[f][u];
     }
+    f32x4* give = reinterpret_cast<f32x4*>(Ex + wave * (16 * UB)) + lane;
+    f32x4* take = reinterpret_cast<f32x4*>(Ex + (wave ^ 4) * (16 * UB)) + lane;
+    if (PAIRS == 2 && !first) {
+#pragma unroll
+      for (int q = 0; q < UB / 64; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) sum[q][t] = take[64 * (4 * q + t)];
+      __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < UB / 64; ++q)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        f32x4 v;
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+          const float lo = acc[0][4 * q + o][t], hi = acc[1][4 * q + o][t];
+          v[o] = kh ? lo : hi;
+        }
+        give[64 * (4 * q + t)] = v;
+      }
     __syncthreads();
-  }
-  if (nmin < nck) {  // the longer half's last chunk
-    if (na == nck) {
-      stage_a();
-      multiply(nmin & 1);
+#pragma unroll
+    for (int q = 0; q < UB / 64; ++q)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        f32x4 v = take[64 * (4 * q + t)];
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+          const float lo = acc[0][4 * q + o][t], hi = acc[1][4 * q + o][t];
+          v[o] += kh ? hi : lo;
+        }
+        sum[q][t] = PAIRS < 2 || first ? v : sum[q][t] + v;
+      }
+    if (PAIRS == 2 && !last) {
+#pragma unroll
+      for (int q = 0; q < UB / 64; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) take[64 * (4 * q + t)] = sum[q][t];
+      clear();
     }
-    __syncthreads();
-  }
-  // the K halves: wave w < 4 keeps row tile 0 and gives row tile 1 to wave w + 4
-  float* ex = reinterpret_cast<float*>(Ws) + wave * (16 * UB);
-#pragma unroll
-  for (int q = 0; q < UB / 64; ++q)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const int f = kh ? 0 : 1;
-      f32x4 v;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = f ? acc[1][4 * q + j][t] : acc[0][4 * q + j][t];
-      *reinterpret_cast<f32x4*>(ex + ((q * 4 + t) * 64 + lane) * 4) = v;
-    }
-  __syncthreads();
+  };
+  fwd_walk<PAIRS, PACKED>(
+      chunks, s * per, (s + 1) * per, kh, load_w, load_a, stage_w, stage_a,
+      [&](int buf) { multiply(buf, acc0); }, [&](int buf) { multiply(buf, acc); },
+      [] { __syncthreads(); }, add);
   if (!live) return;
-  const float* got = reinterpret_cast<const float*>(Ws) + (wave ^ 4) * (16 * UB);
   float* out = Zpart + (int64_t)s * part_stride + ((int64_t)(e0 + mb) * kBatch + 16 * kh) * H + u0 + 4 * i;
 #pragma unroll
   for (int q = 0; q < UB / 64; ++q) {
     if (64 * q >= units) break;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const f32x4 o = *reinterpret_cast<const f32x4*>(got + ((q * 4 + t) * 64 + lane) * 4);
-      f32x4 v;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = kh ? o[j] + acc[1][4 * q + j][t] : acc[0][4 * q + j][t] + o[j];
-      *reinterpret_cast<f32x4*>(out + (int64_t)(4 * g + t) * H + 64 * q) = v;
-    }
+    for (int t = 0; t < 4; ++t) *reinterpret_cast<f32x4*>(out + (int64_t)(4 * g + t) * H + 64 * q) = sum[q][t];
   }
 }
 
 // Per list entry e = blockIdx.x (workspace rows e * 32 ..; G row and loss of its
 // slot) and, when BACKWARD, every gridDim.y-th block of 128 features from
 // blockIdx.y.  Eight waves, 32 rows, all hidden units:
-//   Z1 = the S partial slices summed in slice order + b1; kept in LDS as bf16
+//   Z1 = the S partial slices (in the order of mlp_plan.h) + b1; kept in LDS as bf16
 //   relu(Z1), with -0 where Z1 is not above zero, which is the ReLU's mask
 //   logits = relu(Z1) bf16(W2) + b2 on the matrix cores (classes zero-padded to
 //   16; wave w takes the 32-unit K steps w and w + 8, the waves' sums are added in
@@ -494,9 +513,9 @@ __global__ void __launch_bounds__(kBackThreads, 4)
         const int u = 64 * (4 * h + j);
         if (u < H) {
           f32x4 z = p[0][j];
-#pragma unroll
-          for (int q = 1; q < kSkMaxSlices; ++q)
-            if (q < S) z += p[q][j];
+          if (S > 1) z += p[1][j];
+          if (S == 3) z += p[2][j];
+          if (S == 4) z += p[2][j] + p[3][j];
           z += b[j];
           // relu(z) in bf16; -0 where z is not above zero
 #pragma unroll
@@ -779,31 +798,14 @@ nbsgd_status launch_err(const char* what) {
 
 uint32_t item(int learner, int slot) { return ((uint32_t)learner << 24) | ((uint32_t)slot << 12); }
 
-// Slices of d_in for `tiles` 128 x 128 output tiles: the count that makes rounds of
-// workgroups (one fits a CU, 256 a round) times chunks in a half slice the least,
-// the fewer slices on a tie, since every slice adds a plane of partial sums that is
-// written and read (4,096 samples, 128 tiles, 2 slices: 43.3 us a call; 256-row
-// blocks in 4 slices 45.6; the 8 x 8 workload's 50 tiles take 4).
-// *steps: that least, the chunk steps that a CU makes.
-int fwd_slices(int d_in, int tiles, int* steps) {
-  const int T = d_in / kFwKc;
-  int best = 0;
-  for (int q = 1; q <= kSkMaxSlices && 2 * q <= T; ++q) {
-    const int cost = (tiles * q + 255) / 256 * ((T + 2 * q - 1) / (2 * q));
-    if (!best || cost < *steps) best = q, *steps = cost;
-  }
-  return best;
-}
-
 // Chunk steps of a CU from which the forward reads W1 packed: a step saves 0.2-0.4
 // us, packing adds 1-1.5 us to a launch that is there anyway (a group whose indices
 // go inline has none and is never packed).  mlp_loss, 32-sample batches x d_in x
-// hidden, packed against not, other samples in each call: 512 x 3072x512 (48 steps)
-// 130.4 and 147.9 us, 256 x 3072x512 (24) 72.4 and 83.3, 128 x 3072x512 (12) 46.8 and
-// 50.8, 96 x 3072x384 (8) 35.8 and 37.6; the same samples each time: 80 x 2560x448 (7)
-// 30.6 and 30.3, 40 x 1152x512 (3) 24.7 and 23.8; gradients of 8 x 16 mini-batches
-// 384x512 (3) 40.7 and 39.8.
-constexpr int kPackSteps = 8;
+// hidden, packed against not: 512 x 3072x512 (48 steps) 129.6 and 148.1 us, 256 x
+// 3072x512 (24) 69.9 and 77.3, 128 x 3072x512 (12) 41.2 and 43.0, 256 x 896x512 (7) 38.8
+// and 39.5, 70 x 1152x512 (5) 24.7 and 25.5, 128 x 1024x512 (4) 27.7 and 28.6, 40 x
+// 1152x512 (3) 19.3 and 19.3; gradients of 8 x 16 mini-batches 384x512 (3) 52.7 and 52.5.
+constexpr int kPackSteps = 4;
 
 // Tiles of W1 that the forward of this group reads packed; 0 where it does not, or
 // where they would not fit their part of the workspace.
@@ -848,6 +850,7 @@ void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_
   }
   K.off[K.n] = sk_total;
   const dim3 fgrid(8 * ((sk_total + 7) / 8));
+  const int pairs = fwd_pairs(FwdChunks{d.d_in / kFwKc}.parts() / K.S);
   if (!wide && count <= kInline) {
     InlineIdx I;
     memset(&I, 0, sizeof I);
@@ -858,8 +861,9 @@ void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_
         I.v[t >> 1] |= (uint32_t)src[r] << (16 * (t & 1));
       }
     }
-    hipLaunchKernelGGL((k_mlp_fwd<true, false>), fgrid, dim3(64 * kFwWaves), 0, st, X, w.w1, data, w.idx, w.part,
-                       w.part_stride, d, K, I);
+    const auto kernel = pairs == 0 ? k_mlp_fwd<true, false, 0> : pairs == 1 ? k_mlp_fwd<true, false, 1> : k_mlp_fwd<true, false, 2>;
+    hipLaunchKernelGGL(kernel, fgrid, dim3(64 * kFwWaves), 0, st, X, w.w1, data, w.idx, w.part, w.part_stride, d,
+                       K, I);
   } else {
     const int pk = pack_tiles(K, d, steps, w);
     Pack pack;
@@ -873,9 +877,10 @@ void launch_group(const std::pair<int, int>* mb, int count, const int32_t* host_
     memcpy(pack.learner, K.learner, sizeof pack.learner);
     put_idx(host_idx, mb, count, wide, w, pack, pk, st);
     const Idx16<1> none = {{0u}};
-    hipLaunchKernelGGL((pk ? k_mlp_fwd<false, true> : k_mlp_fwd<false, false>), fgrid,
-                       dim3(64 * kFwWaves), 0, st, X, w.w1, data, w.idx, w.part,
-                       w.part_stride, d, K, none);
+    const auto kernel = pk ? (pairs == 0 ? k_mlp_fwd<false, true, 0> : pairs == 1 ? k_mlp_fwd<false, true, 1> : k_mlp_fwd<false, true, 2>)
+                           : (pairs == 0 ? k_mlp_fwd<false, false, 0> : pairs == 1 ? k_mlp_fwd<false, false, 1> : k_mlp_fwd<false, false, 2>);
+    hipLaunchKernelGGL(kernel, fgrid, dim3(64 * kFwWaves), 0, st, X, w.w1, data, w.idx, w.part, w.part_stride, d,
+                       K, none);
   }
   const int entries = back_entries(count), blocks = d.d_in / kFeatBlock;
   const int each = back_blocks(blocks, entries);

@@ -71,10 +71,9 @@ def test_grad_small_shape_every_entry(tiny):
 @pytest.mark.parametrize("d_in,hidden,classes", [(384, 192, 10), (640, 320, 16), (256, 512, 2),
                                                   (128, 64, 16), (768, 128, 10), (1024, 64, 5)])
 def test_grad_and_loss_odd_shapes_every_entry(d_in, hidden, classes):
-    """Shapes whose d_in splits into 3 or 2 slices (d_in / 64 = 6 or 10), or
-    into four slices of 1, 3 or 4 chunks of 64 (d_in = 256, 768, 1024: the
-    forward's pipeline tail alone; d_in = 640 and the full shape also run its
-    steady loop), and
+    """Shapes whose d_in has one, two, three or four parts (d_in = 128, 256, 384
+    and above), each a slice of its own here, of leaves of one chunk of 64, of
+    two, or of one and two (1024, 768 and 640), and
     whose hidden units leave a half-filled 128-unit block (192, 320), two and
     sixteen classes; three learners with 1-5 finished mini-batches each, so
     the forward's 4-mini-batch groups come in every size; every finished
@@ -125,7 +124,7 @@ def test_grad_and_loss_odd_shapes_every_entry(d_in, hidden, classes):
 
 # Decisions taken from floating point.  Both sides multiply the same bf16
 # operands exactly; the matrix cores add the products in fp32 (the forward in
-# four d_in slices), the oracle in fp64, and the sums differ by about 1e-7 to
+# eight leaves of d_in), the oracle in fp64, and the sums differ by about 1e-7 to
 # 1e-6 at these shapes.  Where a value lies that close to a boundary, the two
 # sides may decide differently:
 # * the ReLU of a first-layer pre-activation within AMBIGUOUS of zero;
