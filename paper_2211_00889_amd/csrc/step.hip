@@ -38,8 +38,6 @@
 #include <stdint.h>
 #include <string.h>
 
-#include <algorithm>
-
 #include "internal.h"
 #include "plan.h"
 #include "tiles.h"
@@ -383,13 +381,18 @@ template <int ORDER>
 void launch_step(float* X, float* V, const float* G, int64_t P, int64_t ld, int n, float mu,
                  const StepPlan& S, int runs, const Mixing& W, hipStream_t s) {
   const size_t lds = (size_t)(n + runs) * 4 * kWave * sizeof(float);
-  const bool ev = even_rows(P, ld);
-  // Rows that together fit half of the 256 MB memory-side cache are likely to be
-  // there (the gradient kernels wrote G, the last step X and V) and are read
-  // through the caches; more than that only evicts itself.  Measured (n = 8, m = 8
-  // ring, three working sets in turn): 84 MB 18.4 -> 16.9 us, 192 MB 38.3 -> 38.2,
-  // 336 MB 61.8 -> 68.3.
-  const bool cached = 4 * P * (S.prefix[n] + 4 * (int64_t)n) <= (int64_t)128 << 20;
+  constexpr bool server = ORDER == kServer;
+  // rows of the replica step, read and written: the finished ones of G, X and V both ways
+  const int64_t rows = S.prefix[n] + 4 * (int64_t)n;
+  const bool ev = even_step(P, ld, server ? rows - 2 * (n - 1) : rows, server);
+  // A step that moves little is likely to find its rows in the 256 MB memory-side
+  // cache (the gradient kernels wrote G, the last step X and V) and reads them through
+  // the caches; more than that only evicts itself.  The limit is on the replica step's
+  // bytes.  Measured by them (n = 8, m = 8 ring, three working sets in turn): 84 MB
+  // 18.4 -> 16.9 us, 192 MB 38.3 -> 38.2, 336 MB 61.8 -> 68.3.  The server's form moves
+  // 2 n - 2 rows fewer and keeps the limit: 132 MB of its own (n = 8, P = 500,032) 25.1
+  // -> 27.3 us, 116 MB 23.8 -> 24.1, 69 MB 15.5 -> 14.9.
+  const bool cached = 4 * P * rows <= (int64_t)128 << 20;
   const auto kernel = ev ? (cached ? k_step<ORDER, true, true> : k_step<ORDER, true, false>)
                          : (cached ? k_step<ORDER, false, true> : k_step<ORDER, false, false>);
   hipLaunchKernelGGL(kernel,

@@ -2,8 +2,8 @@
 // in plain C++ so that the CPU tests walk the same code.
 //
 // Every kernel of step.hip has two forms.  EVEN: P is a multiple of 4 and rows
-// start on 128-byte lines; every lane takes four columns.  Otherwise rows may
-// start on any float: whole tiles of 4 * LANES columns still move 16 bytes a
+// start on 128-byte lines (or on 16 bytes, where a step moves few rows: even_step);
+// every lane takes four columns.  Otherwise rows may start on any float: whole tiles of 4 * LANES columns still move 16 bytes a
 // lane (float-aligned), and the columns after them are taken one float a lane
 // by tiles of LANES.  Measured (n = 8, m = 8, ring step, contiguous rows) against
 // float lanes for odd P and float2 lanes for twice-odd P: P = 11,181,641 987 ->
@@ -25,6 +25,19 @@ namespace nbsgd {
 
 // The EVEN form, for rows ld floats apart.
 inline bool even_rows(int64_t P, int64_t ld) { return P % 4 == 0 && ld % 32 == 0; }
+
+// The form of a fused step that moves `rows` rows (reads and writes), the server's or
+// the replicas'.  Rows off the lines but whole in 16 bytes lose by the neighbouring
+// tiles where few rows are moved, and gain where many are; the line lies between,
+// and for the server, which writes half as many of its rows, farther up.  EVEN against
+// the other form: replicas, 22 rows (n = 2, P = 4,000,004) 86.8 and 94.0 us, 28 (n = 4,
+// 4,383,948) 104.6 and 109.4, 41 (n = 8) 148.4 and 149.2, 36 (n = 1) 132.2 and 127.6, 42
+// (n = 4) 141.9 and 132.7, 80 (n = 8, 1,578,508) 99.6 and 90.7; server, 66 (n = 8,
+// 1,578,508) 80.3 and 87.5, 94 (n = 8, 2,000,004) 146.7 and 151.5, 113 (n = 4) 173.3 and
+// 179.2, 129 (n = 16) 207.3 and 198.2, 153 (n = 8) 242.4 and 232.0.
+inline bool even_step(int64_t P, int64_t ld, int64_t rows, bool server) {
+  return even_rows(P, ld) || (P % 4 == 0 && ld % 4 == 0 && rows < (server ? 124 : 36));
+}
 
 // Column tile of workgroup b of `tiles`: where rows do not start on lines, XCD x
 // (workgroups b % 8 == x) takes kNear neighbouring tiles in a row, so that a

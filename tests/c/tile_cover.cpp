@@ -40,6 +40,15 @@ int main() {
     if (even_rows(P, P) && P % 32) return std::printf("even rows of %lld\n", (long long)P), 1;
   }
   if (even_rows(6, 32) || even_rows(8, 9) || !even_rows(8, 32)) return std::printf("even_rows\n"), 1;
+  // the form of a step: 16-byte rows off the lines by the rows it moves, odd ones never
+  for (int64_t rows : {5, 35, 36, 123, 124, 400})
+    for (bool server : {false, true}) {
+      const bool few = rows < (server ? 124 : 36);
+      if (even_step(1578508, 1578508, rows, server) != few || even_step(1000, 1004, rows, server) != few ||
+          !even_step(1000, 1024, rows, server) || even_step(1578506, 1578508, rows, server) ||
+          even_step(1000, 1001, rows, server))
+        return std::printf("form of a step of %lld rows\n", (long long)rows), 1;
+    }
   std::puts("ok");
   return 0;
 }
