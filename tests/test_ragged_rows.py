@@ -1,7 +1,10 @@
 """Rows of any length and alignment through the step kernels: 16-byte tiles and
 the float tiles after them (csrc/tiles.h).  On the CPU the tiles themselves,
 compiled with g++ and walked; on the GPU every entry point at the tiles' edges
-against the oracle and, bit for bit, against the same columns on aligned rows."""
+against the oracle and, bit for bit, against the same columns on aligned rows; and
+every form of the fused step (whole rows of four columns or ragged ones, read through
+the caches or streamed), bit for bit against the same columns in windows that all
+take one form."""
 
 import os
 import shutil
@@ -34,10 +37,7 @@ def test_tiles_cover_every_column_once(tmp_path):
 # single floats.
 EDGES = [(1, 1), (255, 255), (256, 257), (257, 288), (1023, 1023), (1024, 1028), (1025, 1025),
          (1027, 1056), (8191, 8191), (8192, 8193), (8193, 8224), (8449, 8449), (8446, 8446),
-         (16640, 16644), (33284, 33284),
-         # up to 35 rows of these are above and below the 128 MiB that the step reads
-         # through the caches (the counts decide)
-         (1_000_003, 1_000_003), (1_200_004, 1_200_128)]
+         (16640, 16644), (33284, 33284)]
 
 
 @pytest.mark.gpu
@@ -62,7 +62,7 @@ def test_every_entry_point_at_the_tiles_edges(P, ld):
     for order in (_lib.MIX_THEN_STEP, _lib.STEP_THEN_MIX):
         print(f"[case] step P={P} ld={ld} order={order}", flush=True)
         got = []
-        for stride in (ld, (P + 127) // 128 * 128):  # the second: aligned rows
+        for stride in (ld, (P + 255) // 128 * 128):  # the second: aligned rows, another stride
             Xd, Vd, Gd = rows(X, stride), rows(V, stride), rows(G, stride)
             _lib.step_strided(Xd, Vd, Gd, P, mask, W, 0.1, 0.9, order)
             torch.cuda.synchronize()
@@ -90,3 +90,70 @@ def test_every_entry_point_at_the_tiles_edges(P, ld):
     Xo, Vo = oracle.step.step(X, V, G, mask, W.astype(np.float64), lr, mu, _lib.MIX_THEN_STEP)
     assert rel_err(Gbar.cpu().numpy(), oracle.step.accumulate(G, mask)) <= TOL
     assert rel_err(Yd.cpu().numpy(), Xo) <= TOL and rel_err(Vd.cpu().numpy(), Vo) <= TOL
+
+
+# (n, m, P, ld, whole rows of four columns, for the server too, streamed).  The counts
+# follow from the case's seed, and the test checks the form they give: n = 5, m = 3
+# moves 25 to 35 rows, the server 17 to 27; n = 9, m = 2 45 to 54 and 29 to 38.
+FORMS = [
+    (5, 3, 900_003, 900_003, False, False, False),
+    (5, 3, 1_400_003, 1_400_003, False, False, True),
+    (5, 3, 1_400_002, 1_400_005, False, False, True),
+    (5, 3, 1_400_004, 1_400_005, False, False, True),
+    (5, 3, 1_400_004, 1_400_004, True, True, True),
+    (5, 3, 900_004, 900_004, True, True, False),
+    (5, 3, 1_400_004, 1_400_032, True, True, True),
+    (9, 2, 800_004, 800_004, False, True, True),
+    (9, 2, 600_004, 600_004, False, True, False),
+    (16, 24, 450_004, 450_004, False, False, True),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,m,P,ld,whole,server_whole,streamed", FORMS)
+def test_every_form_of_the_step(n, m, P, ld, whole, server_whole, streamed):
+    """Columns never interact, so windows of them on line-aligned rows, small enough to
+    go through the caches, give the reference for any form.  The forms that the case
+    names are checked against csrc/tiles.h and step.hip's rules first."""
+    torch = pytest.importorskip("torch")
+    rng = np.random.default_rng(P + ld + n)
+    mask = (np.arange(m)[None, :] < rng.integers(1, m + 1, size=n)[:, None]).astype(np.uint8)
+    rows, c = int(mask.sum()) + 4 * n, int(mask.sum())
+    lines, sixteen = P % 4 == 0 and ld % 32 == 0, P % 4 == 0 and ld % 4 == 0
+    assert whole == (lines or (sixteen and rows < 36))
+    assert server_whole == (lines or (sixteen and c + 2 * n + 2 < 124))
+    assert streamed == (4 * P * rows > 128 << 20)
+    g = torch.Generator(device="cuda:0").manual_seed(P + n)
+
+    def rnd(*shape):
+        return torch.empty(shape, dtype=torch.float32, device="cuda:0").normal_(generator=g)
+
+    X, V, G = rnd(n, ld), rnd(n, ld), rnd(n, m, ld)
+    W = _lib.w_ring(n)
+
+    def window(a, c0, c1):  # line-aligned rows of whole lines, whatever lies past the columns
+        out = torch.zeros(a.shape[:-1] + ((c1 - c0 + 31) // 32 * 32,), dtype=torch.float32, device="cuda:0")
+        out[..., :c1 - c0] = a[..., c0:c1]
+        return out
+
+    def run(step, x, v):
+        """step(x, v, G, columns) on the whole rows and in windows; both ways' x and v."""
+        got = [x.clone(), v.clone()]
+        step(*got, G, P)
+        want = [x.clone(), v.clone()]
+        width = (128 << 20) // (4 * rows) // 32 * 32
+        for c0 in range(0, P, width):
+            c1 = min(P, c0 + width)
+            part = [window(x, c0, c1), window(v, c0, c1)]
+            step(*part, window(G, c0, c1), part[0].shape[-1])
+            for a, b in zip(want, part):
+                a[..., c0:c1] = b[..., :c1 - c0]
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)  # the columns past P too: never written
+
+    for order in (_lib.MIX_THEN_STEP, _lib.STEP_THEN_MIX):
+        print(f"[case] form n={n} m={m} P={P} ld={ld} order={order}", flush=True)
+        run(lambda x, v, gg, cols: _lib.step_strided(x, v, gg, cols, mask, W, 0.1, 0.9, order), X, V)
+    print(f"[case] form n={n} m={m} P={P} ld={ld} server", flush=True)
+    run(lambda x, v, gg, cols: _lib.step_server(x, v, gg, cols, mask, 0.1, 0.9), X[0].clone(), V)
