@@ -58,30 +58,40 @@ def copy_context(nbytes, dev, reps: int = 5):
             "frac": 8 * n / best / 1e9 / PEAK_HBM_GBS}
 
 
-def kernel_code_sha256(path):
-    """sha256 of a source file without its // comments and blank lines: the
+# What decides the fused step's traffic: the kernel, the tiles and forms it takes, and
+# the planner that distributes the rows.
+STEP_SOURCES = ("step.hip", "tiles.h", "plan.cpp", "plan.h")
+
+
+def kernel_code_sha256(*paths):
+    """sha256 of source files without their // comments and blank lines: the
     key of a committed counter summary, which stays valid while only
     comments change."""
     import hashlib
     import re
 
     lines = []
-    with open(path) as f:
-        for line in f.read().split("\n"):
-            line = re.sub(r"//.*$", "", line).rstrip()
-            if line:
-                lines.append(line)
+    for path in paths:
+        with open(path) as f:
+            for line in f.read().split("\n"):
+                line = re.sub(r"//.*$", "", line).rstrip()
+                if line:
+                    lines.append(line)
     return hashlib.sha256("\n".join(lines).encode()).hexdigest()
+
+
+def step_code_sha256(csrc=os.path.join(ROOT, "paper_2211_00889_amd", "csrc")):
+    return kernel_code_sha256(*(os.path.join(csrc, name) for name in STEP_SOURCES))
 
 
 def measured_traffic(wl):
     """HBM bytes per launch of the fused kernel from the committed rocprofv3
     PMC summary (FETCH_SIZE and WRITE_SIZE, each scaled by what the counter
     reads for a plain 1 GiB copy), or None when there is no summary for this
-    workload or the kernel code changed since the counters were taken."""
+    workload or the step's code changed since the counters were taken."""
     import glob
 
-    sha = kernel_code_sha256(os.path.join(ROOT, "paper_2211_00889_amd", "csrc", "step.hip"))
+    sha = step_code_sha256()
     for path in glob.glob(os.path.join(ROOT, "profiles", "k_step_traffic_*.json")):
         with open(path) as f:
             rec = json.load(f)

@@ -32,6 +32,25 @@ def test_source_hash_ignores_comments_and_blank_lines(tmp_path):
     assert bench.kernel_code_sha256(a) != bench.kernel_code_sha256(c)
 
 
+@pytest.mark.parametrize("name,code", [("tiles.h", "constexpr uint32_t kNear = 4;"),
+                                       ("plan.h", "constexpr int kStepWaves = 8;"),
+                                       ("plan.cpp", "namespace nbsgd {"), ("step.hip", "constexpr int kChunk = 16;")])
+def test_any_source_of_the_step_invalidates_the_counters(tmp_path, name, code):
+    """A change to the step's kernel, tiles or planner changes the key that the
+    committed traffic counters are found by; a comment does not."""
+    csrc = os.path.join(ROOT, "paper_2211_00889_amd", "csrc")
+    for f in os.listdir(csrc):
+        (tmp_path / f).write_text(open(os.path.join(csrc, f)).read())
+    before = bench.step_code_sha256(str(tmp_path))
+    assert before == bench.step_code_sha256()
+    text = (tmp_path / name).read_text()
+    assert code in text
+    (tmp_path / name).write_text("// a comment\n" + text)
+    assert bench.step_code_sha256(str(tmp_path)) == before
+    (tmp_path / name).write_text(text.replace(code, "constexpr int kChanged = 1;\n" + code))
+    assert bench.step_code_sha256(str(tmp_path)) != before
+
+
 @pytest.mark.parametrize("path", sorted(glob.glob(os.path.join(ROOT, "profiles", "k_step_traffic_*.json"))))
 def test_committed_traffic_records_are_consistent(path):
     """Scaled traffic = raw counters x the calibration copy's scale; the scale
