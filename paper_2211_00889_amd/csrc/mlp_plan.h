@@ -86,8 +86,8 @@ struct FwdPos {
 // us so, 132.8 with code of its own; where W1 is not packed the loop spills and loses:
 // 200 x 640x448 39.5 and 38.0).
 constexpr int fwd_pairs(int parts) { return parts < 3 ? parts - 1 : 2; }
-template <int PAIRS, bool ROLLED, class LoadW, class LoadA, class StageW, class StageA, class FirstLeaf, class Leaf, class Barrier,
-          class Add>
+template <int PAIRS, bool ROLLED, class LoadW, class LoadA, class StageW, class StageA, class FirstLeaf,
+          class Leaf, class Barrier, class Add>
 NBSGD_HD void fwd_walk(FwdChunks k, int p, int end, int h, LoadW load_w, LoadA load_a, StageW stage_w,
                        StageA stage_a, FirstLeaf first_leaf, Leaf leaf, Barrier barrier, Add add) {
   FwdPos w = {k.pair(p, end), 0}, a = w;  // the steps last loaded
@@ -154,9 +154,9 @@ inline int fwd_slice_steps(FwdChunks k, int S) {
 // chunk steps and four the least, the fewer slices on a tie.  A round's first chunks
 // and its exchange of sums take as long as four steps, and every slice adds a plane of
 // partial sums that is written and read.  Losses of 32-sample batches of 3072x512 in
-// 1, 2 and 4 slices: 40 52.7, 31.1, 25.5 us; 64 54.8, 36.3, 32.4; 68 56.6, 37.2, 41.6;
-// 128 58.3, 43.1, 51.3; 160 58.9, 64.2, 67.3; 300 116, 102, 112; 400 122, 131, 149.
-// 86 of 384x512 in 1 and 3 slices 25.9 and 28.6; 300 of 256x512 in 1 and 2 42.1, 46.5.
+// 1, 2 and 4 slices: 40 50.7, 31.9, 24.9 us; 64 53.4, 36.1, 30.8; 68 54.7, 36.6, 41.7;
+// 128 55.1, 41.9, 50.6; 160 58.6, 66.1, 67.3; 300 114, 105, 113; 400 122, 135, 150.
+// 86 of 384x512 in 1 and 3 slices 22.8 and 25.2; 300 of 256x512 in 1 and 2 35.8, 41.4.
 // *steps: the chunk steps that a CU makes.
 constexpr int kFwRound = 4;
 inline int fwd_slices(int d_in, int tiles, int* steps) {
